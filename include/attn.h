@@ -67,9 +67,7 @@ typedef struct {
  * then Wqkv and Wo repacked into the fragment-tiled layout
  * of moe.h's experts, the query and key rows of Wqkv reordered within each
  * head so that the two members of every rotation pair share a 16-row tile),
- * of the key/value cache, and of the workspace (which, when max_tokens > 16,
- * also holds a small tile table that attn_init writes); 0 if cfg is
- * invalid.  Cache layout, per layer l: K then V, each bf16
+ * of the key/value cache, and of the workspace; 0 if cfg is invalid.  Cache layout, per layer l: K then V, each bf16
  * [n_kv_heads][max_seq][head_dim] (head-major, positions contiguous), so K of
  * layer l head g position p starts at element
  * ((l * 2 + 0) * n_kv_heads + g) * max_seq * head_dim + p * head_dim.  A
@@ -80,10 +78,8 @@ MOE_API size_t attn_workspace_bytes(const attn_config *cfg);
 
 /* Sec. 4.1's persistent buffers, applied to the block: validates cfg and
  * records the three caller-allocated device buffers (256-byte aligned, kept
- * until attn_destroy).  Allocates only the host-side context; when
- * max_tokens > 16 it also copies the prefill tile table into the workspace
- * (a synchronous copy; MOE_E_HIP if it fails).  Errors as moe_init; the
- * message is readable through attn_last_error(NULL). */
+ * until attn_destroy).  Allocates only the host-side context.  Errors as
+ * moe_init; the message is readable through attn_last_error(NULL). */
 MOE_API moe_status attn_init(const attn_config *cfg, void *weight_arena, void *kv_cache,
                              void *workspace, attn_ctx **out);
 

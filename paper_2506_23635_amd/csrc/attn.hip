@@ -658,6 +658,7 @@ struct RopeArgs {
     uint16_t* kc;
     uint16_t* vc;
     int T, H, G, hd, max_seq, pos0;
+    int n_split;           // qkvp is [n_split][T][nqkv] partial sums, added in order
 };
 
 __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a)
@@ -667,11 +668,17 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a)
     const int nqk = (a.H + a.G) * hd, nqkv = nqk + a.G * hd;
     const int pos = a.pos0 + t;
     const float* src = a.qkvp + (int64_t)t * nqkv;
+    const int64_t part = (int64_t)a.T * nqkv;
+    auto load = [&](int i) {
+        float v = src[i];
+        for (int k = 1; k < a.n_split; ++k) v += src[k * part + i];
+        return v;
+    };
     float* nat = a.qkv + (int64_t)t * nqkv;
     for (int e = threadIdx.x; e < (a.H + a.G) * half; e += blockDim.x) {
         const int head = e / half, f = e % half;
         const int n0 = head * hd + f, n1 = n0 + half;
-        const float x0 = src[moe::rope_row(n0, hd)], x1 = src[moe::rope_row(n1, hd)];
+        const float x0 = load(moe::rope_row(n0, hd)), x1 = load(moe::rope_row(n1, hd));
         nat[n0] = x0;
         nat[n1] = x1;
         float c, sf;
@@ -683,7 +690,7 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a)
         dst[f + half] = moe::f32_to_bf16(r1);
     }
     for (int e = threadIdx.x; e < a.G * hd; e += blockDim.x) {
-        const float v = src[nqk + e];
+        const float v = load(nqk + e);
         nat[nqk + e] = v;
         a.vc[((int64_t)(e / hd) * a.max_seq + pos) * hd + e % hd] = moe::f32_to_bf16(v);
     }
@@ -940,14 +947,29 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
 
 // y = bf16(x + o), 8 elements per thread
 __global__ __launch_bounds__(256) void residual_kernel(const uint16_t* __restrict__ x,
-                                                       const float* __restrict__ o,
+                                                       float* o, const float* op, int n_split,
                                                        uint16_t* y, int64_t n8)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n8) return;
     const u32x4_t xv = ld16(x + i * 8);
-    const float4 o0 = *reinterpret_cast<const float4*>(o + i * 8);
-    const float4 o1 = *reinterpret_cast<const float4*>(o + i * 8 + 4);
+    float4 o0, o1;
+    if (n_split > 1) {
+        o0 = *reinterpret_cast<const float4*>(op + i * 8);
+        o1 = *reinterpret_cast<const float4*>(op + i * 8 + 4);
+        for (int k = 1; k < n_split; ++k) {
+            const float* pk = op + (k * n8 + i) * 8;
+            const float4 p0 = *reinterpret_cast<const float4*>(pk);
+            const float4 p1 = *reinterpret_cast<const float4*>(pk + 4);
+            o0.x += p0.x; o0.y += p0.y; o0.z += p0.z; o0.w += p0.w;
+            o1.x += p1.x; o1.y += p1.y; o1.z += p1.z; o1.w += p1.w;
+        }
+        *reinterpret_cast<float4*>(o + i * 8) = o0;
+        *reinterpret_cast<float4*>(o + i * 8 + 4) = o1;
+    } else {
+        o0 = *reinterpret_cast<const float4*>(o + i * 8);
+        o1 = *reinterpret_cast<const float4*>(o + i * 8 + 4);
+    }
     const float ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
     u32x4_t out;
 #pragma unroll
@@ -1016,9 +1038,9 @@ hipError_t attn_launch_score(const uint16_t* q, const uint16_t* kc, const uint16
 
 hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qkv, uint16_t* q,
                             uint16_t* kc, uint16_t* vc, int T, int H, int G, int hd, int max_seq,
-                            int pos0, hipStream_t s)
+                            int pos0, int n_split, hipStream_t s)
 {
-    attn::RopeArgs a{qkvp, inv_freq, qkv, q, kc, vc, T, H, G, hd, max_seq, pos0};
+    attn::RopeArgs a{qkvp, inv_freq, qkv, q, kc, vc, T, H, G, hd, max_seq, pos0, n_split};
     hipLaunchKernelGGL(attn::rope_kernel, dim3(T), dim3(256), 0, s, a);
     return hipGetLastError();
 }
@@ -1038,12 +1060,12 @@ hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16
     return hipGetLastError();
 }
 
-hipError_t attn_launch_residual(const uint16_t* x, const float* o, uint16_t* y, int64_t n,
-                                hipStream_t s)
+hipError_t attn_launch_residual(const uint16_t* x, float* o, const float* op, int n_split,
+                                uint16_t* y, int64_t n, hipStream_t s)
 {
     const int64_t n8 = n / 8;
     hipLaunchKernelGGL(attn::residual_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s,
-                       x, o, y, n8);
+                       x, o, op, n_split, y, n8);
     return hipGetLastError();
 }
 

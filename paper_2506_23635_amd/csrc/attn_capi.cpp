@@ -33,8 +33,8 @@ struct Layout {
     size_t gamma_bytes, freq_off, gamma2_off, wqkv_off, wqkv_bytes, wo_off, wo_bytes, layer_bytes,
         arena_bytes;
     size_t cache_head_elems, cache_layer_bytes, cache_bytes;
-    size_t h_off, qkv_off, q_off, part_off, a_off, o_off, qkvp_off, plan_off, ws_bytes;
-    int nqkv, nq, n_chunks, max_tiles;
+    size_t h_off, qkv_off, q_off, part_off, a_off, o_off, qkvp_off, ws_bytes;
+    int nqkv, nq, n_chunks;
 };
 
 const char* check_config(const attn_config* c)
@@ -82,8 +82,6 @@ Layout make_layout(const attn_config* c)
     L.n_chunks = attn_chunks(c->max_seq);
     const size_t Tm = c->max_tokens;
     const size_t Td = std::min<size_t>(Tm, kDecodeTokens);
-    const int tile_rows = moe_prefill_tile_rows();
-    L.max_tiles = (int)((Tm + tile_rows - 1) / tile_rows);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
     L.h_off = take(Tm * d * 2);
@@ -93,10 +91,15 @@ Layout make_layout(const attn_config* c)
     L.a_off = take(Tm * L.nq * 2);
     L.o_off = take(Tm * d * 4);
     if (Tm > (size_t)kDecodeTokens) {
-        L.qkvp_off = take(Tm * L.nqkv * 4);
-        // the projection GEMMs' tile table: (0, 256 i) per token tile, then
-        // per T: offsets {0, T} and the tile count
-        L.plan_off = take((size_t)L.max_tiles * 8 + (Tm + 1) * 16);
+        // the projections' outputs in packed row order, or their partial sums
+        // over ranges of the reduction
+        size_t rows_q = Tm, rows_o = 0;
+        for (int T = 1; T <= (int)Tm; ++T) {
+            const int so = moe_gemm_plain_split(T, (int)d);
+            rows_q = std::max(rows_q, (size_t)moe_gemm_plain_split(T, L.nqkv) * T);
+            if (so > 1) rows_o = std::max(rows_o, (size_t)so * T);
+        }
+        L.qkvp_off = take(std::max(rows_q * L.nqkv, rows_o * d) * 4);
     }
     L.ws_bytes = off;
     return L;
@@ -166,26 +169,24 @@ uint16_t* layer_v(attn_ctx* c, int l)
 }
 
 // One plain GEMM out = in W^T on the grouped GEMM's down mode: a single
-// "expert" whose rows are the T tokens, its weight the packed N x K matrix.
-hipError_t project(attn_ctx* c, const uint8_t* wpk, const uint16_t* in, int K, int N, float* out,
-                   int T, hipStream_t s)
+// "expert" whose rows are the T tokens, its weight the packed N x K matrix;
+// with split > 1 partial sums over `split` ranges of K at out + i T N.
+hipError_t project(const uint8_t* wpk, const uint16_t* in, int K, int N, float* out, int T,
+                   int split, hipStream_t s)
 {
-    const Layout& L = c->L;
-    int32_t* plan = reinterpret_cast<int32_t*>(c->ws + L.plan_off);
     moe::GemmArgs g{};
     g.experts = wpk;
     g.expert_bytes = (uint64_t)N * K * 2;
-    g.gu_bytes = 0;
     g.H = const_cast<uint16_t*>(in);
     g.O = out;
-    g.tiles = plan;
-    g.offsets = plan + (size_t)L.max_tiles * 2 + (size_t)T * 4;
-    g.n_tiles = g.offsets + 2;
     g.d = N;
     g.f = K;
-    g.e_begin = 0;
-    g.max_tiles = (T + moe_prefill_tile_rows() - 1) / moe_prefill_tile_rows();
+    g.n_local = 1;
     g.T = T;
+    g.max_rows = T;
+    g.mid = moe_gemm_mid_tiles(T, 1, 1, 1, N);
+    g.k_split = split;
+    g.split_stride = (uint64_t)T * N;
     return moe_launch_gemm_down(&g, s);
 }
 
@@ -204,17 +205,18 @@ moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int
     uint16_t* a = reinterpret_cast<uint16_t*>(ctx->ws + L.a_off);
     float* o = reinterpret_cast<float*>(ctx->ws + L.o_off);
     const int d = c.d_model;
+    const int sq = moe_gemm_plain_split(T, L.nqkv), so = moe_gemm_plain_split(T, d);
     const float* gamma = reinterpret_cast<const float*>(w);
     hipError_t e = timed(ctx, ATTN_K_NORM, s, [&] {
         return attn_launch_norm(x, gamma, T, d, c.norm_eps, h, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "norm kernel launch");
-    e = timed(ctx, ATTN_K_QKV, s, [&] { return project(ctx, w + L.wqkv_off, h, d, L.nqkv, qkvp, T, s); });
+    e = timed(ctx, ATTN_K_QKV, s, [&] { return project(w + L.wqkv_off, h, d, L.nqkv, qkvp, T, sq, s); });
     if (e != hipSuccess) return hip_fail(ctx, e, "projection GEMM launch");
     e = timed(ctx, ATTN_K_ROPE, s, [&] {
         return attn_launch_rope(qkvp, reinterpret_cast<const double*>(w + L.freq_off), qkv, q,
                                 layer_k(ctx, layer), layer_v(ctx, layer), T, c.n_heads,
-                                c.n_kv_heads, c.head_dim, c.max_seq, pos0, s);
+                                c.n_kv_heads, c.head_dim, c.max_seq, pos0, sq, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "rotation kernel launch");
     e = timed(ctx, ATTN_K_SCORE, s, [&] {
@@ -222,10 +224,10 @@ moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int
                                  c.n_kv_heads, c.head_dim, c.max_seq, pos0, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "attention kernel launch");
-    e = timed(ctx, ATTN_K_OUT, s, [&] { return project(ctx, w + L.wo_off, a, L.nq, d, o, T, s); });
+    e = timed(ctx, ATTN_K_OUT, s, [&] { return project(w + L.wo_off, a, L.nq, d, so > 1 ? qkvp : o, T, so, s); });
     if (e != hipSuccess) return hip_fail(ctx, e, "output projection GEMM launch");
     e = timed(ctx, ATTN_K_RESIDUAL, s, [&] {
-        return attn_launch_residual(x, o, y, (int64_t)T * d, s);
+        return attn_launch_residual(x, o, qkvp, so, y, (int64_t)T * d, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "residual kernel launch");
     return MOE_OK;
@@ -331,23 +333,6 @@ moe_status attn_init(const attn_config* cfg, void* weight_arena, void* kv_cache,
     c->arena = static_cast<uint8_t*>(weight_arena);
     c->cache = static_cast<uint8_t*>(kv_cache);
     c->ws = static_cast<uint8_t*>(workspace);
-    if (cfg->max_tokens > kDecodeTokens) {
-        // the prefill projections' tile table, written once into the workspace
-        const int tile_rows = moe_prefill_tile_rows();
-        std::vector<int32_t> plan((size_t)c->L.max_tiles * 2 + ((size_t)cfg->max_tokens + 1) * 4, 0);
-        for (int i = 0; i < c->L.max_tiles; ++i) plan[2 * i + 1] = i * tile_rows;
-        for (int T = 0; T <= cfg->max_tokens; ++T) {
-            int32_t* e = &plan[(size_t)c->L.max_tiles * 2 + (size_t)T * 4];
-            e[1] = T;
-            e[2] = (T + tile_rows - 1) / tile_rows;
-        }
-        const hipError_t e = hipMemcpy(c->ws + c->L.plan_off, plan.data(), plan.size() * 4,
-                                       hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            delete c;
-            return fail(nullptr, MOE_E_HIP, std::string("tile table copy: ") + hipGetErrorString(e));
-        }
-    }
     c->loaded.assign(cfg->n_layers, 0);
     c->post_loaded.assign(cfg->n_layers, 0);
     c->prof_on = false;

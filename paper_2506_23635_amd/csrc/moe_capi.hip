@@ -282,7 +282,7 @@ moe_status run_experts(moe_ctx* ctx, const WsView& ws, int layer, const uint16_t
         e = timed(ctx, MOE_K_DECODE_DOWN, s, [&] { return moe_launch_decode_down(&a, slots, s); });
         if (e != hipSuccess) return hip_fail(ctx, e, "decode down kernel launch");
     } else {
-        moe::GemmArgs a;
+        moe::GemmArgs a{};
         a.experts = experts;
         a.expert_bytes = ctx->L.expert_bytes;
         a.gu_bytes = ctx->L.gu_bytes;
@@ -291,20 +291,22 @@ moe_status run_experts(moe_ctx* ctx, const WsView& ws, int layer, const uint16_t
         a.O = O;
         a.offsets = ws.rv.offsets;
         a.row_token = ws.rv.row_token;
-        a.tiles = ws.rv.tiles;
-        a.n_tiles = ws.rv.n_tiles;
         a.d = c.d_model;
         a.f = c.ffn_dim;
         a.e_begin = c.expert_begin;
+        a.n_local = c.n_local_experts;
         a.T = T;
+        a.max_rows = T * std::min(c.top_k, c.n_local_experts);
+        a.k_split = 1;
         a.max_stamps = ctx->tl_max;
-        const int tile_rows = moe_prefill_tile_rows();
-        const int kl = std::min(c.top_k, c.n_local_experts);
-        a.max_tiles = (T * kl + tile_rows - 1) / tile_rows + c.n_local_experts;
+        // a timeline is that of the 256 x 256 tiles
+        const bool timeline = ctx->tl_gateup || ctx->tl_down;
+        a.mid = !timeline && moe_gemm_mid_tiles(T, c.top_k, c.n_experts, c.n_local_experts, 2 * c.ffn_dim);
         a.stamps = ctx->tl_gateup;
         e = timed(ctx, MOE_K_GEMM_GATEUP, s, [&] { return moe_launch_gemm_gateup(&a, s); });
         if (e != hipSuccess) return hip_fail(ctx, e, "grouped GEMM gate/up kernel launch");
         a.stamps = ctx->tl_down;
+        a.mid = !timeline && moe_gemm_mid_tiles(T, c.top_k, c.n_experts, c.n_local_experts, c.d_model);
         e = timed(ctx, MOE_K_GEMM_DOWN, s, [&] { return moe_launch_gemm_down(&a, s); });
         if (e != hipSuccess) return hip_fail(ctx, e, "grouped GEMM down kernel launch");
     }

@@ -128,12 +128,14 @@ struct GemmArgs {
     const uint16_t* x;        // [T, d]
     uint16_t* H;              // [rows, f]
     float* O;                 // [rows, d]
-    const int32_t* offsets;   // [E + 1]
+    const int32_t* offsets;   // [E + 1], or NULL: one expert, its rows 0 .. T - 1 (kDown)
     const int32_t* row_token; // [rows]
-    const int32_t* tiles;     // [max_tiles][2] = (expert, first row)
-    const int32_t* n_tiles;   // [1]
-    int d, f, e_begin, max_tiles;
+    int d, f, e_begin, n_local;
     int T;                    // tokens of the call (rows of x)
+    int max_rows;             // most rows the call can have
+    int mid;                  // take the 128 x 128 tiles, where
+    int k_split;              // ... the reduction of a kDown is cut in k_split ranges, ...
+    uint64_t split_stride;    // ... range i's sums at O + i * split_stride
     uint64_t* stamps;         // per-workgroup timeline [max_stamps][8], or NULL (measurement)
     int max_stamps;
 };
@@ -165,6 +167,8 @@ hipError_t moe_launch_decode_down(const moe::DecodeArgs* a, int n_slots, hipStre
 hipError_t moe_launch_gemm_gateup(const moe::GemmArgs* a, hipStream_t s);
 hipError_t moe_launch_gemm_down(const moe::GemmArgs* a, hipStream_t s);
 int moe_prefill_tile_rows();
+int moe_gemm_mid_tiles(int T, int k, int E, int n_local, int M);
+int moe_gemm_plain_split(int T, int M);
 hipError_t moe_launch_combine(const float* O, const int32_t* pair_row, const float* topk_w, int T,
                               int d, int k, uint16_t* y, float* y32, uint16_t* x_residual,
                               hipStream_t s);
@@ -183,11 +187,11 @@ hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N
                            const uint16_t* res, uint16_t* y16, hipStream_t s);
 hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qkv, uint16_t* q,
                             uint16_t* kc, uint16_t* vc, int T, int H, int G, int hd, int max_seq,
-                            int pos0, hipStream_t s);
+                            int pos0, int n_split, hipStream_t s);
 hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16_t* vc,
                              uint16_t* out, int T, int H, int G, int hd, int max_seq, int pos0,
                              hipStream_t s);
-hipError_t attn_launch_residual(const uint16_t* x, const float* o, uint16_t* y, int64_t n,
+hipError_t attn_launch_residual(const uint16_t* x, float* o, const float* op, int n_split, uint16_t* y, int64_t n,
                                 hipStream_t s);
 int attn_chunks(int n_pos);
 int attn_part_stride(int hd);

@@ -23,15 +23,18 @@
 //  - An expert's partial last token tile skips the MFMAs of token-block
 //    pairs past its last row (the padding waste is under 64 rows).
 //  - Workgroups are numbered so that consecutive tiles (same weight slab,
-//    consecutive token tiles) land on the same XCD and share its L2.
+//    consecutive token tiles) land on the same XCD and share its L2
+//    (find_tile).
 //
 // gemm<kGateUp>: A = GU slab (gate and up row tiles interleaved), X = the
 //   expert's rows of x gathered through row_token; epilogue
 //   H = bf16(silu(G) * U) (paper Table tab:vars (e): w1 gate, v1 up).
 // gemm<kDown>:   A = DN slab, X = the expert's rows of H; epilogue O fp32.
 //
-// Token tiles (expert, first grouped row) come from the routing kernel; the
-// grid is sized for the worst case and surplus workgroups exit at once.
+// Token tiles come from the routing's row offsets; the grid is sized for the
+// worst case and surplus workgroups, all at its end, exit at once.  Few rows
+// per expert take smaller tiles (gemm_mid_kernel below).
+#include <algorithm>
 #include <type_traits>
 
 #include "moe_common.h"
@@ -259,11 +262,8 @@ __device__ __forceinline__ void tile_loop(const TileCtx& c, int n_pairs, uint8_t
 
 // One BM x BN tile (feature tile ft, token tile tt) of the grouped GEMM.
 template <int kMode>
-__device__ __forceinline__ void process_tile(const GemmArgs& a, int ft, int tt, uint8_t* lds)
+__device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_start, int row_end, int ft, uint8_t* lds)
 {
-    const int e = a.tiles[2 * tt];
-    const int row_start = a.tiles[2 * tt + 1];
-    const int row_end = min(row_start + BN, a.offsets[e + 1]);
     const int ntb = (row_end - row_start + 31) / 32;   // 32-token blocks with rows
 
     const int K = kMode == kGateUp ? a.d : a.f;
@@ -373,76 +373,400 @@ __device__ __forceinline__ void process_tile(const GemmArgs& a, int ft, int tt, 
     }
 }
 
+// Measurement only (a.stamps, set by moe_profile_gemm_timeline): workgroup
+// blockIdx.x's record of one tile, [0], [1] the constant 100 MHz counter and
+// [2], [3] the shader-clock counter around the tile.
+__device__ __forceinline__ void write_stamp(const GemmArgs& a, uint64_t r0, uint64_t c0, int ft,
+                                            int tt, int rows, int e)
+{
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const uint64_t r1 = __builtin_amdgcn_s_memrealtime();
+    const uint64_t c1 = __builtin_amdgcn_s_memtime();
+    uint32_t hw, xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw));
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    uint64_t* out = a.stamps + (uint64_t)blockIdx.x * 8;
+    out[0] = r0;
+    out[1] = r1;
+    out[2] = c0;
+    out[3] = c1;
+    out[4] = (uint64_t)hw | ((uint64_t)xcc << 32);
+    out[5] = (uint64_t)ft | ((uint64_t)tt << 16) | ((uint64_t)rows << 32) | ((uint64_t)e << 48);
+}
+
+// Numbering: hardware hands block b to XCD b % 8.  Position b / 8 of an
+// XCD's sequence takes, expert by expert, one token tile on every eighth
+// feature tile, the expert's token tiles fastest: all XCDs stream one
+// expert's weights at a time, each keeps that expert's token rows in its
+// L2, and the token tiles of an expert read a weight slab through one L2
+// one right after the other.  The tiles are counted from the experts' row
+// offsets (lane i: local expert i), so that every block up to the last
+// tile is live: with blocks for the largest possible count per expert,
+// an XCD, which deals its blocks to its shader engines and CUs in turn,
+// left up to half of them without a live one (237 workgroups running at a
+// time of the 512 that fit).
+struct TilePos {
+    int el;            // local expert, or -1 past the last tile
+    int first, rows;   // its rows
+    int n_sub, sub;    // its token tiles, and this one
+    int ft;            // feature tile
+};
+
+__device__ __forceinline__ TilePos find_tile(const GemmArgs& a, int block, int n_ftiles, int tile_rows)
+{
+    const int n_fg = (n_ftiles + kXcds - 1) / kXcds;
+    const int pos = block / kXcds;
+    const int lane = threadIdx.x & 63;
+    int first = 0, rows = 0;
+    if (a.offsets == nullptr) {              // a plain product: T rows
+        rows = lane == 0 ? a.T : 0;
+    } else if (lane < a.n_local) {
+        first = a.offsets[a.e_begin + lane];
+        rows = a.offsets[a.e_begin + lane + 1] - first;
+    }
+    const int n_sub = (rows + tile_rows - 1) / tile_rows;
+    int upto = n_sub;                        // token tiles of the experts up to this lane's
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int v = __shfl_up(upto, off, kWave);
+        if (lane >= off) upto += v;
+    }
+    TilePos t{};
+    t.el = __ffsll((unsigned long long)__ballot(pos / n_fg < upto)) - 1;
+    if (t.el < 0) return t;
+    t.first = __builtin_amdgcn_readlane(first, t.el);
+    t.rows = __builtin_amdgcn_readlane(rows, t.el);
+    t.n_sub = __builtin_amdgcn_readlane(n_sub, t.el);
+    const int in_e = pos - (__builtin_amdgcn_readlane(upto, t.el) - t.n_sub) * n_fg;
+    t.sub = in_e % t.n_sub;
+    t.ft = in_e / t.n_sub * kXcds + block % kXcds;
+    return t;
+}
+
 template <int kMode>
 __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kRingB * B_STAGE_BYTES];
     const int M = kMode == kGateUp ? 2 * a.f : a.d;   // a multiple of BM
     const int n_ftiles = M / BM;
-    // XCD-aware numbering: hardware hands block b to XCD b % 8; each XCD
-    // gets a contiguous run of logical tiles (feature tile major, token tile
-    // fastest over the max_tiles slots the grid is sized for), so the
-    // workgroups running together on an XCD work on consecutive token tiles
-    // of one feature slab and share the weight slabs of their experts (A) in
-    // its L2.  Slots past the routing's token tiles exit at once.  (Splitting
-    // only the live tiles evenly over the XCDs measured no better: the XCDs'
-    // finish times differ by the mix of full and partial tiles they get.)
-    const int per_xcd = gridDim.x / kXcds;
-    const int logical = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    const int ft = logical / a.max_tiles, tt = logical % a.max_tiles;
-    if (ft >= n_ftiles || tt >= *a.n_tiles) return;
-    // measurement only (a.stamps set by moe_profile_gemm_timeline): the
-    // constant 100 MHz counter and the shader-clock counter around the tile
+    const TilePos tp = find_tile(a, blockIdx.x, n_ftiles, BN);
+    if (tp.el < 0 || tp.ft >= n_ftiles) return;
+    const int ft = tp.ft, tt = tp.sub, e = a.e_begin + tp.el;
+    const int row_start = tp.first + tp.sub * BN, row_end = min(row_start + BN, tp.first + tp.rows);
     const bool stamp = a.stamps != nullptr && (int)blockIdx.x < a.max_stamps;
     uint64_t r0 = 0, c0 = 0;
     if (stamp) {
         r0 = __builtin_amdgcn_s_memrealtime();
         c0 = __builtin_amdgcn_s_memtime();
     }
-    process_tile<kMode>(a, ft, tt, lds);
-    if (stamp) {
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint64_t r1 = __builtin_amdgcn_s_memrealtime();
-            const uint64_t c1 = __builtin_amdgcn_s_memtime();
-            uint32_t hw, xcc;
-            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw));
-            asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-            const int e = a.tiles[2 * tt], row0 = a.tiles[2 * tt + 1];
-            const int rows = min(row0 + BN, a.offsets[e + 1]) - row0;
-            uint64_t* out = a.stamps + (uint64_t)blockIdx.x * 8;
-            out[0] = r0;
-            out[1] = r1;
-            out[2] = c0;
-            out[3] = c1;
-            out[4] = (uint64_t)hw | ((uint64_t)xcc << 32);
-            out[5] = (uint64_t)ft | ((uint64_t)tt << 16) | ((uint64_t)rows << 32) |
-                     ((uint64_t)e << 48);
+    process_tile<kMode>(a, e, row_start, row_end, ft, lds);
+    if (stamp) write_stamp(a, r0, c0, ft, tt, row_end - row_start, e);
+}
+
+// ---------------------------------------------------------------------------
+// Few rows per expert (or few tokens in a plain projection): the same GEMM on
+// 128-feature x 128-row tiles.
+//
+// Here the kernel is bound by the weight stream, and 256 x 256 tiles are too
+// few and too long: their last wave leaves CUs idle, and one wave per SIMD
+// with three stages of weights in flight does not reach the read rate.  Four
+// waves take 32 features each (one MFMA block) of up to four 32-token blocks
+// in at most 256 registers and 64 KiB of LDS, so two workgroups share a CU; A
+// runs four 64-K stages ahead in registers, B three ahead in LDS.  Token
+// blocks that a tile does not have are neither loaded nor multiplied (the
+// loop is instantiated for 1 to 4 blocks).  Weights that one tile alone reads
+// are loaded nontemporal: the plain policy streams at 6.2 TB/s, the
+// nontemporal one at 6.9 (the same addresses, 4 GiB); where several tiles
+// share a weight slab it is loaded plain, so that it stays in the L2 for the
+// next one.
+constexpr int MBM = 128;           // features per workgroup tile
+constexpr int MBN = 128;           // token rows per workgroup tile
+constexpr int kMidTB = MBN / 32;   // 32-token blocks at most
+constexpr int kMidRing = 4;        // A stages in registers
+constexpr int kMidRingB = 4;       // B stages in LDS
+constexpr int kNonTemporal = 2;    // buffer cache policy
+
+struct MidCtx {
+    __amdgpu_buffer_rsrc_t a_rsrc, b_rsrc;
+    uint32_t a_off;            // this lane's A byte offset at the first stage
+    uint32_t b_off[kMidTB];    // byte offsets in b_rsrc of this lane's 16-byte chunk, per load
+    uint32_t rd_off[KS];       // LDS byte offsets of this lane's B fragment piece, per K step
+    int n_stages, w;
+    uint32_t s0;               // first stage of the workgroup's K range
+};
+
+// Stage s multiplies A(s) (registers) with B(s) (LDS buffer s % 4).  B
+// fragments are read one K step ahead, across stages too: before the last K
+// step the wave waits for its own reads of this stage's buffer and for its
+// part of B(s+1), then a barrier publishes both.  At its start stage s issues
+// B(s+3) into the buffer that stage s-1 read; A(s+4) refills each fragment
+// after its last use.  Vector-memory operations complete in order: after
+// B(s+1), issued at the start of stage s-2, came the four A refills of that
+// stage, the B loads and A refills of stage s-1, and the B loads and the
+// first three A refills of stage s.  Past the last full round of four stages
+// there are no A refills (the compiler would drop them as dead), so only the
+// B loads are counted.  B loads past the last stage re-read it into a buffer
+// that no later stage reads.
+template <int kTB, bool kOnce>
+__device__ __forceinline__ void mid_loop(const MidCtx& c, uint8_t* lds, f32x16_t (&acc)[kMidTB])
+{
+    constexpr int kStage = kTB * 32 * BK * 2;
+    constexpr int kWaitMid = wait_vm(2 * kTB + 3 * KS - 1), kWaitMidTail = wait_vm(2 * kTB);
+    const int n_stages = c.n_stages, w = c.w;
+    u32x4_t ra[kMidRing][KS];
+    auto load_a1 = [&](int s, int j, u32x4_t& dst) {
+        dst = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                              c.a_rsrc, c.a_off + (j / 2) * kTileBytes + (j % 2) * (kTileBytes / 2),
+                                              (c.s0 + (uint32_t)s) * (2 * kTileBytes), kOnce ? kNonTemporal : 0));
+    };
+    // load q of wave w: rows 32 q + 8 w .. + 7, whole 128-byte lines
+    auto load_b = [&](int s, int buf) {
+#pragma unroll
+        for (int q = 0; q < kTB; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                c.b_rsrc,
+                (__attribute__((address_space(3))) void*)(&lds[buf + (q * 4 + w) * kTileBytes]),
+                16, c.b_off[q], (c.s0 + (uint32_t)s) * (BK * 2), 0, 0);
+    };
+    u32x4_t bw[2][kTB];                        // B fragments of two K steps in turn
+    auto read_b = [&](int buf, int j, u32x4_t (&dst)[kTB]) {
+#pragma unroll
+        for (int t = 0; t < kTB; ++t)
+            dst[t] = *reinterpret_cast<const u32x4_t*>(&lds[buf + c.rd_off[j] + t * 32 * (BK * 2)]);
+    };
+    int cur = 0, prev = (kMidRingB - 1) * kStage;   // byte offsets of this and the last stage's buffer
+    auto stage = [&](int s, u32x4_t (&A)[KS], auto tail) {
+        constexpr bool kTail = decltype(tail)::value;
+        const int next = cur + kStage == kMidRingB * kStage ? 0 : cur + kStage;
+        const int sa = min(s + kMidRing, n_stages - 1);
+        load_b(min(s + kMidRingB - 1, n_stages - 1), prev);
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            if (j + 1 == KS) {
+                // this wave's reads of the stage's buffer and its part of B(s+1)
+                __builtin_amdgcn_s_waitcnt((kTail ? kWaitMidTail : kWaitMid) & ~(0xF << 8));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                read_b(next, 0, bw[0]);
+            } else {
+                read_b(cur, j + 1, bw[(j + 1) & 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < kTB; ++t) acc[t] = mfma32x32x16(A[j], bw[j & 1][t], acc[t]);
+            if (!kTail) load_a1(sa, j, A[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        prev = cur;
+        cur = next;
+    };
+    // A first: its addresses do not wait for the row gather
+#pragma unroll
+    for (int i = 0; i < kMidRing; ++i)
+#pragma unroll
+        for (int j = 0; j < KS; ++j) load_a1(min(i, n_stages - 1), j, ra[i][j]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i + 1 < kMidRingB; ++i) load_b(min(i, n_stages - 1), i * kStage);
+    __builtin_amdgcn_s_waitcnt(kWaitAll);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read_b(0, 0, bw[0]);
+    int s = 0;
+    for (; s + kMidRing <= n_stages; s += kMidRing) {
+        stage(s + 0, ra[0], std::false_type{});
+        stage(s + 1, ra[1], std::false_type{});
+        stage(s + 2, ra[2], std::false_type{});
+        stage(s + 3, ra[3], std::false_type{});
+    }
+    if (s < n_stages) stage(s, ra[0], std::true_type{});
+    if (s + 1 < n_stages) stage(s + 1, ra[1], std::true_type{});
+    if (s + 2 < n_stages) stage(s + 2, ra[2], std::true_type{});
+    // drain the dummy B loads before the workgroup's LDS can be handed on
+    __builtin_amdgcn_s_waitcnt(kWaitAll);
+    __builtin_amdgcn_s_barrier();
+}
+
+template <bool kOnce>
+__device__ __forceinline__ void mid_loop_any(int tb, const MidCtx& c, uint8_t* lds, f32x16_t (&acc)[kMidTB])
+{
+    if (tb == 1)
+        mid_loop<1, kOnce>(c, lds, acc);
+    else if (tb == 2)
+        mid_loop<2, kOnce>(c, lds, acc);
+    else if (tb == 3)
+        mid_loop<3, kOnce>(c, lds, acc);
+    else
+        mid_loop<4, kOnce>(c, lds, acc);
+}
+
+template <int kMode>
+__global__ __launch_bounds__(kThreads, 2) void gemm_mid_kernel(GemmArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kMidRingB * MBN * BK * 2];
+    const int n_ftiles = (kMode == kGateUp ? 2 * a.f : a.d) / MBM;
+    const TilePos tp = find_tile(a, blockIdx.x, n_ftiles * a.k_split, MBN);
+    if (tp.el < 0) return;
+    const int split = tp.ft / n_ftiles, ft = tp.ft % n_ftiles;
+    if (split >= a.k_split) return;
+    const int e = a.e_begin + tp.el;
+    // an expert's 32-token blocks spread evenly over its token tiles
+    const int per_sub = ((tp.rows + 31) / 32 + tp.n_sub - 1) / tp.n_sub * 32;
+    const int row_start = tp.first + tp.sub * per_sub;
+    const int row_end = min(row_start + per_sub, tp.first + tp.rows);
+    if (row_start >= row_end) return;
+    const int tb = (row_end - row_start + 31) / 32;   // 32-token blocks with rows
+
+    const int K = kMode == kGateUp ? a.d : a.f;
+    const uint64_t KT = (uint64_t)K / kTileK;
+    const uint8_t* wbase = a.experts + (uint64_t)(e - a.e_begin) * a.expert_bytes +
+                           (kMode == kGateUp ? 0 : a.gu_bytes);
+    const int lane = threadIdx.x & 63;
+    MidCtx c;
+    c.w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = c.w, n_all = K / BK;
+    c.s0 = (uint32_t)(n_all * split / a.k_split);
+    c.n_stages = n_all * (split + 1) / a.k_split - (int)c.s0;
+    const uint64_t rt = (uint64_t)ft * (MBM / 16) + w * 2;   // the wave's two 16-row weight tiles
+    const uint64_t slab_bytes = kMode == kGateUp ? a.gu_bytes : a.expert_bytes - a.gu_bytes;
+    c.a_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(wbase), 0, (int)slab_bytes,
+                                                 kBufferFlags);
+    c.a_off = (uint32_t)tile_offset(rt + ((lane & 31) >> 4), 0, KT) +
+              (uint32_t)(((lane >> 5) * 16) + (lane & 15)) * 16;
+    if (kMode == kGateUp)
+        c.b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.x), 0,
+                                                     a.T * a.d * 2, kBufferFlags);
+    else
+        c.b_rsrc = __builtin_amdgcn_make_buffer_rsrc(a.H + (int64_t)row_start * a.f, 0,
+                                                     (row_end - row_start) * a.f * 2, kBufferFlags);
+#pragma unroll
+    for (int q = 0; q < kMidTB; ++q) {
+        const int R = q * 32 + w * 8 + (lane >> 3);
+        const int row = row_start + R;
+        const int rr = row < row_end ? row : row_start;   // rows past the end: any valid row
+        const uint32_t chunk = (uint32_t)((lane & 7) ^ b_swizzle(R)) * 16;
+        if (kMode == kGateUp)
+            c.b_off[q] = (uint32_t)a.row_token[rr] * (uint32_t)a.d * 2 + chunk;
+        else
+            c.b_off[q] = (uint32_t)(rr - row_start) * (uint32_t)a.f * 2 + chunk;
+    }
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+        const int R = lane & 31;
+        c.rd_off[j] = (uint32_t)R * (BK * 2) + (uint32_t)(((2 * j + (lane >> 5)) ^ b_swizzle(R)) * 16);
+    }
+    f32x16_t acc[kMidTB];
+#pragma unroll
+    for (int t = 0; t < kMidTB; ++t) acc[t] = f32x16_t{};
+    if (tp.n_sub == 1)
+        mid_loop_any<true>(tb, c, lds, acc);
+    else
+        mid_loop_any<false>(tb, c, lds, acc);
+
+    // epilogue as gemm_kernel's
+    const int half = lane >> 5;
+#pragma unroll
+    for (int t = 0; t < kMidTB; ++t) {
+        const int row = row_start + t * 32 + (lane & 31);
+        if (t >= tb || row >= row_end) continue;
+        const f32x16_t v = acc[t];
+        if (kMode == kGateUp) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const int feat = (int)(rt / 2) * 16 + 8 * g + 4 * half;
+                const uint32_t h01 = cvt_pk_bf16(silu_mul(v[4 * g + 0], v[4 * g + 8]),
+                                                 silu_mul(v[4 * g + 1], v[4 * g + 9]));
+                const uint32_t h23 = cvt_pk_bf16(silu_mul(v[4 * g + 2], v[4 * g + 10]),
+                                                 silu_mul(v[4 * g + 3], v[4 * g + 11]));
+                *reinterpret_cast<uint2*>(a.H + (int64_t)row * a.f + feat) = make_uint2(h01, h23);
+            }
+        } else {
+            float* out = a.O + (uint64_t)split * a.split_stride + (int64_t)row * a.d;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int feat = (int)rt * 16 + 8 * g + 4 * half;
+                *reinterpret_cast<float4*>(out + feat) =
+                    make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+            }
         }
     }
 }
 
 }  // namespace moe
 
-extern "C" int moe_prefill_tile_rows() { return moe::BN; }
+extern "C" {
+
+int moe_prefill_tile_rows() { return moe::BN; }
+
+// Whether a grouped GEMM of M features per expert takes the 128 x 128 tiles:
+// T tokens, k of E experts each, n_local experts here (a plain product: k =
+// E = n_local = 1).
+//  - Up to about 112 rows per expert the weight stream bounds it (d 6144, f
+//    10752, all 16 experts, whole layer, 256 x 256 tiles -> 128 x 128: 17
+//    tokens 1129 -> 965 us, 128 tokens 1220 -> 1048, 400 tokens (100 rows)
+//    1288 -> 1214; 500 tokens (125 rows) 1338 -> 1496).
+//  - With at most 128 tiles of 256 x 256 half of the CUs or more would have
+//    none (d 6144: 600 tokens through the 8192-wide projection, 96 tiles,
+//    and the 6144-wide one, 72 tiles, the attention block 272 -> 216 us; 1024
+//    tokens, 128 and 96 tiles, 318 -> 304; 1400 tokens, 192 and 144 tiles,
+//    355 -> 411).
+int moe_gemm_mid_tiles(int T, int k, int E, int n_local, int M)
+{
+    const int64_t pairs = (int64_t)T * k;
+    if (pairs <= (int64_t)112 * E) return 1;
+    const int64_t rows = (pairs + E - 1) / E;
+    return (int64_t)(M / moe::BM) * n_local * ((rows + moe::BN - 1) / moe::BN) <= 128;
+}
+
+// Ranges of the reduction of a plain product on 128 x 128 tiles: two where
+// the tiles leave half of the CUs idle (d 6144, the attention block: 64
+// tokens, 64 and 48 tiles, 144 -> 117 us; 200 tokens, 128 and 96 tiles, 147 ->
+// 113; 300 tokens, 192 and 144 tiles, 188 -> 195).
+int moe_gemm_plain_split(int T, int M)
+{
+    if (!moe_gemm_mid_tiles(T, 1, 1, 1, M)) return 1;
+    return (int64_t)(M / moe::MBM) * ((T + moe::MBN - 1) / moe::MBN) <= 128 ? 2 : 1;
+}
+
+}  // extern "C"
+
+// Token tiles of tile_rows rows that a call can have: full ones and one
+// partial tile per expert.
+static int launch_tiles(const moe::GemmArgs* a, int tile_rows)
+{
+    return std::min(a->max_rows, a->max_rows / tile_rows + a->n_local);
+}
 
 template <int kMode>
 static hipError_t launch_gemm(const moe::GemmArgs* a, hipStream_t s)
 {
     const int M = kMode == moe::kGateUp ? 2 * a->f : a->d;
-    const int n = M / moe::BM * a->max_tiles;
-    const int grid = (n + moe::kXcds - 1) / moe::kXcds * moe::kXcds;
+    const int grid = launch_tiles(a, moe::BN) * ((M / moe::BM + moe::kXcds - 1) / moe::kXcds) * moe::kXcds;
     hipLaunchKernelGGL((moe::gemm_kernel<kMode>), dim3(grid), dim3(moe::kThreads), 0, s, *a);
+    return hipGetLastError();
+}
+
+template <int kMode>
+static hipError_t launch_gemm_mid(const moe::GemmArgs* a, hipStream_t s)
+{
+    const int M = kMode == moe::kGateUp ? 2 * a->f : a->d;
+    const int n_ft = M / moe::MBM * a->k_split;
+    const int grid = launch_tiles(a, moe::MBN) *
+                     ((n_ft + moe::kXcds - 1) / moe::kXcds) * moe::kXcds;
+    hipLaunchKernelGGL((moe::gemm_mid_kernel<kMode>), dim3(grid),
+                       dim3(moe::kThreads), 0, s, *a);
     return hipGetLastError();
 }
 
 extern "C" hipError_t moe_launch_gemm_gateup(const moe::GemmArgs* a, hipStream_t s)
 {
-    return launch_gemm<moe::kGateUp>(a, s);
+    return a->mid ? launch_gemm_mid<moe::kGateUp>(a, s) : launch_gemm<moe::kGateUp>(a, s);
 }
 
 extern "C" hipError_t moe_launch_gemm_down(const moe::GemmArgs* a, hipStream_t s)
 {
-    return launch_gemm<moe::kDown>(a, s);
+    return a->mid ? launch_gemm_mid<moe::kDown>(a, s) : launch_gemm<moe::kDown>(a, s);
 }
 
