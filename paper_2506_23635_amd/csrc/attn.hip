@@ -9,25 +9,31 @@
 //                   of the query and key heads (angles reduced in fp64,
 //                   rotation in fp32): bf16 q to the workspace, bf16 k and v
 //                   appended to the cache
-//   score_kernel    attention of every query head of one key/value head over
+//   score_kernel    up to 16 query rows per key/value head and 1024 positions:
+//                   attention of every query head of one key/value head over
 //                   one chunk of 64 positions (4 waves): scores on the matrix
 //                   cores, the chunk's softmax maximum and sum, and the
 //                   unnormalised weighted sum of v
 //   combine_kernel  merges the chunks of each (token, head) into bf16 a
+//   flash_kernel    otherwise: attention on the matrix cores, the rows of a
+//                   key/value head's whole group together, over one or
+//                   several position ranges
+//   merge_kernel    merges the ranges into bf16 a
 //   gemv_kernel     o = a Wo (fp32) and y = bf16(x + o)
 //
 // Above 16 new tokens (prefill) the block is: norm_kernel -> q|k|v on the
 // grouped GEMM of moe_prefill.hip -> rope_kernel (rotation, cache append)
-// -> flash_kernel (causal attention on the matrix cores) -> o = a Wo on the
+// -> flash_kernel (and merge_kernel or merge_few_kernel) -> o = a Wo on the
 // grouped GEMM -> residual_kernel.
 //
 // The GEMVs stream the fragment-tiled weights (the layout of moe_common.h)
 // through v_mfma_f32_16x16x32_bf16 with the tokens as the B operand, as the
 // MoE decode GEMVs do: one workgroup per 16 output features, its 8 waves
 // splitting K (wave w takes K tiles w, w + 8, ...), wave 0 adding the
-// partial fragments in wave order.  In the attention, q . k of 16 positions
-// and 16 query rows is one MFMA per 32 dims; the weighted sum of v is VALU
-// work, small beside the projections' weight stream.
+// partial fragments in wave order.
+#include <algorithm>
+#include <cmath>
+
 #include "moe_common.h"
 
 namespace attn {
@@ -40,7 +46,7 @@ using moe::kTileRows;
 
 constexpr int kSplit = 8;          // waves per GEMV workgroup (K split)
 constexpr int kUnroll = 8;         // K tiles per wave in flight
-constexpr int kChunk = 64;         // positions per attention workgroup
+constexpr int kChunk = 64;         // positions per score_kernel workgroup
 constexpr int kPartPad = 4;        // m, l and padding after the hd sums of a partial
 
 __device__ inline u32x4_t ld16_nt(const void* p)
@@ -460,7 +466,9 @@ struct ScoreArgs {
     float scale;           // 1 / sqrt(hd)
 };
 
-// One workgroup of 4 waves per (key/value head g, chunk c of 64 positions);
+// The attention of up to 16 query rows per key/value head over at most 1024
+// positions (attn_short).  One workgroup of 4 waves per (key/value head g,
+// chunk c of 64 positions);
 // wave w owns positions 16 w .. 16 w + 15 of the chunk.  The query rows are
 // every (token t, query head j of g), r = t * group + jj, in batches of 16;
 // row r sees positions up to pos0 + t (causal).
@@ -696,37 +704,48 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a)
     }
 }
 
-// flash_kernel: causal attention of T new tokens, one workgroup of 4 waves
-// per (query head j, block of 128 query tokens); wave w owns tokens
-// 32 w .. 32 w + 31 of the block, one per lane column (lanes l and l + 32
-// share token l % 32).  Per step of 64 positions of head j's key/value head:
-// K rows and V transposed (dims major) go to LDS; the scores are computed
+// flash_kernel: causal attention of T new tokens.  The query rows of one
+// key/value head are the (token, query head of its group) pairs, r = t *
+// group + jj; a workgroup of 4 waves takes a block of 128 or 64 of them
+// (kPG = 1 or 2 position groups: the 4 / kPG waves of a group own 32 rows
+// each) and one of n_split ranges of the positions they need.  Packing the group's
+// heads into the rows reads K and V once for all of them and keeps a block's
+// tokens, so the positions its causal mask wastes, few.
+//
+// Per step of kP positions K rows and V transposed (dims major) go to LDS,
+// and each position group takes kP / kPG of them.  The scores are computed
 // transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16 (A = 32 positions x
 // 16 dims of K from LDS, B = the wave's query rows), so lane l ends with the
-// scores of token l % 32 at positions 8 g + 4 (l / 32) + r of each
-// 32-position block (register 4 g + r); the running maximum and sum per
-// token (one exchange between the lane pair) rescale the output, and
-// O^T += V^T P^T takes the P values straight from those registers as the B
-// operand: the 16-position K step s of a block takes registers g = 2 s,
-// 2 s + 1, i.e. positions 16 s + {4 h .. 4 h + 3, 8 + 4 h .. 8 + 4 h + 3}
-// for h = l / 32, and the V^T operand is read from LDS in the same order.
-// P enters the matrix cores as two bf16 terms, bf16(p) and bf16(p - bf16(p)),
-// which keep 16 significant bits; V is bf16 and every product is exact in
-// the fp32 accumulation.
+// scores of row l % 32 at positions 8 g + 4 (l / 32) + r of each 32-position
+// block (register 4 g + r); the running maximum and sum per row (one
+// exchange between the lane pair) rescale the output, and O^T += V^T P^T
+// takes the P values straight from those registers as the B operand: the
+// 16-position K step s of a block takes registers g = 2 s, 2 s + 1, i.e.
+// positions 16 s + {4 h .. 4 h + 3, 8 + 4 h .. 8 + 4 h + 3} for h = l / 32,
+// and the V^T operand is read from LDS in the same order.  P enters the
+// matrix cores as kTerms bf16 terms (each the rounding of what the earlier
+// ones left, which the subtraction gives exactly): three keep all 24 bits
+// (few tokens), two keep 16 (prefill); V is bf16 and every product is exact
+// in the fp32 accumulation.
+//
+// The position groups' sums are merged through LDS in group order.  With one
+// range the result is written as bf16; with several, each writes its
+// unnormalised sums, maximum (base 2) and sum of weights for merge_kernel: a
+// few rows over a long context are split until about two workgroups per CU
+// run (attn_split).
 struct FlashArgs {
     const uint16_t* q;     // [T][H][HD] bf16, rotated
     const uint16_t* kc;    // this layer's K cache [G][max_seq][HD]
     const uint16_t* vc;
     uint16_t* out;         // a [T][H * HD] bf16
+    float* part;           // n_split > 1: [T][H][n_split][HD + kPartPad]: sum of p v, then m, l
     int T, H, G, max_seq, pos0;
-    int nqb;               // query blocks of kFlashQ tokens
+    int nrb;               // row blocks per key/value head
+    int n_split;           // position ranges
     float scale2;          // 1/sqrt(head_dim) * log2(e): scores in base 2
 };
 
 constexpr int kXcds = 8;
-
-constexpr int kFlashQ = 128;    // query tokens per workgroup
-constexpr int kFlashP = 64;     // positions per step
 
 __device__ inline uint32_t pack_bf16x2(float lo, float hi)
 {
@@ -741,69 +760,85 @@ __device__ inline f32x16_t mfma32x32x16(const u32x4_t a, const u32x4_t b, f32x16
                                                    __builtin_bit_cast(moe::bf16x8_t, b), c, 0, 0, 0);
 }
 
-// Two workgroups per CU: 219 registers per lane at head_dim 128 (the output
-// block of 32 tokens x 128 dims alone takes 64), 2 waves per SIMD.
-template <int HD>
+constexpr int flash_rows(int pg) { return 128 / pg; }        // query rows per workgroup
+constexpr int kFlashP = 64;                                  // positions per step
+
+// Two workgroups per CU: at most 256 registers per lane (the output block of
+// 32 rows x 128 dims alone takes 64), 2 waves per SIMD.
+template <int HD, int kPG, int kTerms>
 __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
 {
     constexpr int KQ = HD / 16;              // 16-dim K steps of the score MFMAs
     constexpr int DB = HD / 32;              // 32-dim blocks of the output
+    constexpr int kP = kFlashP;
+    constexpr int NB = kP / 32 / kPG;        // 32-position blocks per wave and step
+    constexpr int kRowWaves = 4 / kPG;       // waves on different rows
     constexpr int KROW = HD + 8;             // padded K row in LDS (bf16)
     // padded V^T row (positions, bf16): 34 words, so the 8-byte reads of
     // consecutive dims fall in distinct bank pairs (LDS bank conflicts 19.5 M
     // -> 6.5 M cycles per launch against 36 words)
-    constexpr int VROW = kFlashP + 4;
-    __shared__ __attribute__((aligned(16))) uint16_t ks[kFlashP * KROW];
-    __shared__ __attribute__((aligned(16))) uint16_t vt[HD * VROW];
+    constexpr int VROW = kP + 4;
+    constexpr int kStageBytes = kP * KROW * 2 + HD * VROW * 2;
+    // merge of the position groups: per wave past the first group DB * 16
+    // sums, the maximum and the weights' sum per lane
+    constexpr int kMergeBytes = (4 - kRowWaves) * (DB * 16 + 2) * 64 * 4;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kStageBytes > kMergeBytes ? kStageBytes : kMergeBytes];
+    uint16_t* ks = reinterpret_cast<uint16_t*>(lds);
+    uint32_t* vt32 = reinterpret_cast<uint32_t*>(lds + kP * KROW * 2);
     // XCD-aware numbering: hardware hands block b to XCD b % 8, and each XCD
-    // takes a contiguous run of the logical order (key/value head, query
-    // block from the last, query head of the group), so the workgroups of
-    // one key/value head share its K and V in one L2 (DBRX: one head per
-    // XCD) and on every XCD the longest query blocks (the most positions)
-    // start first.  Logical slots past the last block exit at once.
-    const int groups = a.H / a.G;
+    // takes a contiguous run of the logical order (key/value head, row block
+    // from the last, position range), so the workgroups of one key/value
+    // head share its K and V in one L2 (DBRX: one head per XCD) and on every
+    // XCD the longest row blocks (the most positions) start first.  Logical
+    // slots past the last block exit at once.
+    const int group = a.H / a.G;
     const int per_xcd = gridDim.x / kXcds;
     const int logical = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (logical >= a.H * a.nqb) return;
-    const int kvh = logical / (a.nqb * groups), rem = logical % (a.nqb * groups);
-    const int qb = a.nqb - 1 - rem / groups;
-    const int j = kvh * groups + rem % groups;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int per_head = a.nrb * a.n_split;
+    if (logical >= a.G * per_head) return;
+    const int kvh = logical / per_head, rem = logical % per_head;
+    const int rb = a.nrb - 1 - rem / a.n_split, split = rem % a.n_split;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 31, h = lane >> 5;
-    const int t_w0 = qb * kFlashQ + w * 32;             // the wave's first token
-    const int t = t_w0 + c;                              // this lane's token
-    const bool tok_ok = t < a.T;
+    const int pg = w / kRowWaves;                        // the wave's position group
+    const int R = a.T * group;
+    const int row_w0 = rb * flash_rows(kPG) + w % kRowWaves * 32;   // the wave's first row
+    const int row = row_w0 + c;                          // this lane's row
+    const bool wave_ok = row_w0 < R, row_ok = row < R;
+    const int t = (row_ok ? row : 0) / group;            // its token and query head
+    const int j = kvh * group + (row_ok ? row : 0) % group;
     const int lim = a.pos0 + t;                          // its last position
+    const int lim_w0 = a.pos0 + row_w0 / group;          // the last position of the wave's first row
     const u32x4_t zero = {0u, 0u, 0u, 0u};
     u32x4_t qf[KQ];
     {
-        const uint16_t* qrow = a.q + ((int64_t)(tok_ok ? t : 0) * a.H + j) * HD + h * 8;
+        const uint16_t* qrow = a.q + ((int64_t)t * a.H + j) * HD + h * 8;
 #pragma unroll
         for (int k = 0; k < KQ; ++k) {
             const u32x4_t v = ld16(qrow + k * 16);
-            qf[k] = tok_ok ? v : zero;
+            qf[k] = row_ok ? v : zero;
         }
     }
     f32x16_t o[DB];
 #pragma unroll
     for (int b = 0; b < DB; ++b) o[b] = f32x16_t{};
     float m = -INFINITY, l = 0.f;
-    const int t_last = min(qb * kFlashQ + kFlashQ, a.T) - 1;
+    const int t_last = (min((rb + 1) * flash_rows(kPG), R) - 1) / group;
     const int n_pos = a.pos0 + t_last + 1;               // positions the block needs
+    const int n_steps = (n_pos + kP - 1) / kP;
+    const int s_end = (int)((int64_t)n_steps * (split + 1) / a.n_split);
     const uint16_t* kbase = a.kc + (int64_t)kvh * a.max_seq * HD;
     const uint16_t* vbase = a.vc + (int64_t)kvh * a.max_seq * HD;
-    uint32_t* vt32 = reinterpret_cast<uint32_t*>(vt);
     // per step a thread stages KL 16-byte pieces of K rows and VL position
-    // pairs of V; all of a step's global loads are issued before the barrier
-    // that frees the LDS, so the step waits for one load latency, not one per
-    // piece
-    constexpr int KL = kFlashP * (HD / 8) / 256;
-    constexpr int VL = (kFlashP / 2) * (HD / 8) / 256;
-    static_assert(KL * 256 == kFlashP * (HD / 8) && VL * 256 == (kFlashP / 2) * (HD / 8),
+    // pairs of V; all of a step's global loads are issued together, before
+    // the barrier that frees the LDS
+    constexpr int KL = kP * (HD / 8) / 256;
+    constexpr int VL = (kP / 2) * (HD / 8) / 256;
+    static_assert(KL * 256 == kP * (HD / 8) && VL * 256 == (kP / 2) * (HD / 8),
                   "the staging pieces divide evenly over the 256 threads");
-    for (int p0 = 0; p0 < n_pos; p0 += kFlashP) {
-        const int live = min(kFlashP, n_pos - p0);
-        u32x4_t kv[KL], va[VL], vb[VL];
+    u32x4_t kv[KL], va[VL], vb[VL];
+    auto fetch = [&](int st) {
+        const int p0 = st * kP, live = min(kP, n_pos - p0);
 #pragma unroll
         for (int i = 0; i < KL; ++i) {
             const int e = threadIdx.x + i * 256;
@@ -813,13 +848,18 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
 #pragma unroll
         for (int i = 0; i < VL; ++i) {
             const int e = threadIdx.x + i * 256;
-            const int pp = e % (kFlashP / 2), k8 = e / (kFlashP / 2);
+            const int pp = e % (kP / 2), k8 = e / (kP / 2);
             va[i] = ld16(vbase + (int64_t)(p0 + min(2 * pp, live - 1)) * HD + k8 * 8);
             vb[i] = ld16(vbase + (int64_t)(p0 + min(2 * pp + 1, live - 1)) * HD + k8 * 8);
         }
+    };
+    int st = (int)((int64_t)n_steps * split / a.n_split);
+    for (; st < s_end; ++st) {
+        const int p0 = st * kP;
+        fetch(st);
         __syncthreads();                                 // the last step's LDS reads are done
         // K rows: 16-byte pieces, coalesced.  Rows past `live` repeat the
-        // last live row (the loads are clamped): every token's causal mask
+        // last live row (the loads are clamped): every row's causal mask
         // removes those positions, so their scores never count and their
         // probabilities are exactly 0 against finite V rows.
 #pragma unroll
@@ -834,7 +874,7 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
 #pragma unroll
         for (int i = 0; i < VL; ++i) {
             const int e = threadIdx.x + i * 256;
-            const int pp = e % (kFlashP / 2), k8 = e / (kFlashP / 2);
+            const int pp = e % (kP / 2), k8 = e / (kP / 2);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 vt32[((k8 * 8 + 2 * r) * VROW) / 2 + pp] = __builtin_amdgcn_perm(vb[i][r], va[i][r], 0x05040100u);
@@ -842,53 +882,55 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
             }
         }
         __syncthreads();
-        // S^T = K Q^T for the two 32-position blocks: lane (c, h) ends with
-        // token c's scores at positions 32 pb + 8 g + 4 h + r (register 4 g + r)
-        f32x16_t st[2];
+        if (!wave_ok) continue;
+        // S^T = K Q^T for the wave's 32-position blocks: lane (c, h) ends with
+        // row c's scores at positions 32 pb + 8 g + 4 h + r (register 4 g + r)
+        f32x16_t sc[NB];
 #pragma unroll
-        for (int pb = 0; pb < 2; ++pb) {
-            st[pb] = f32x16_t{};
+        for (int pb = 0; pb < NB; ++pb) {
+            sc[pb] = f32x16_t{};
 #pragma unroll
             for (int k = 0; k < KQ; ++k) {
-                const u32x4_t kf =
-                    *reinterpret_cast<const u32x4_t*>(&ks[(pb * 32 + c) * KROW + k * 16 + h * 8]);
-                st[pb] = mfma32x32x16(kf, qf[k], st[pb]);
+                const u32x4_t kf = *reinterpret_cast<const u32x4_t*>(
+                    &ks[((pg * NB + pb) * 32 + c) * KROW + k * 16 + h * 8]);
+                sc[pb] = mfma32x32x16(kf, qf[k], sc[pb]);
             }
         }
         // scores in base 2 (s * scale * log2 e, so p = 2^(s2 - m2)); the
-        // causal mask and the tokens past T only on the steps that need them
-        // (wave-uniform: a step past the wave's first token's last position,
-        // or a wave with tokens past T)
-        float sv[32];
+        // causal mask and the rows past R only on the steps that need them
+        // (wave-uniform: a step past the last position of the wave's first
+        // row, or a wave with rows past R)
+        const int pw0 = p0 + pg * NB * 32;               // the wave's first position
+        float sv[NB * 16];
         float mx = -INFINITY;
-        if (p0 + kFlashP - 1 > a.pos0 + t_w0 || t_w0 + 31 >= a.T) {
+        if (pw0 + NB * 32 - 1 > lim_w0 || row_w0 + 31 >= R) {
 #pragma unroll
-            for (int pb = 0; pb < 2; ++pb)
+            for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int pos = p0 + pb * 32 + 8 * (i / 4) + 4 * h + (i % 4);
-                    const float v = (tok_ok && pos <= lim) ? st[pb][i] * a.scale2 : -INFINITY;
+                    const int pos = pw0 + pb * 32 + 8 * (i / 4) + 4 * h + (i % 4);
+                    const float v = (row_ok && pos <= lim) ? sc[pb][i] * a.scale2 : -INFINITY;
                     sv[pb * 16 + i] = v;
                     mx = fmaxf(mx, v);
                 }
         } else {
 #pragma unroll
-            for (int pb = 0; pb < 2; ++pb)
+            for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    sv[pb * 16 + i] = st[pb][i] * a.scale2;
+                    sv[pb * 16 + i] = sc[pb][i] * a.scale2;
                     mx = fmaxf(mx, sv[pb * 16 + i]);
                 }
         }
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float mn = fmaxf(m, mx);
-        // a token with every position masked so far (only tokens past T)
-        // keeps mn = -inf: subtract 0 instead, so its p are 0, not NaN
+        // a row with every position masked so far keeps mn = -inf: subtract
+        // 0 instead, so its p are 0, not NaN
         const float msub = mn == -INFINITY ? 0.f : mn;
         float ps = 0.f;
-        float pv[32];
+        float pv[NB * 16];
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
+        for (int e = 0; e < NB * 16; ++e) {
             pv[e] = __builtin_amdgcn_exp2f(sv[e] - msub);
             ps += pv[e];
         }
@@ -903,46 +945,185 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
         }
         l += ps;
         m = mn;
-        // O^T += V^T P^T, four 16-position K steps: step (pb, s) takes the
-        // lane's registers 4 g + r for g = 2 s, 2 s + 1 of block pb, i.e.
-        // positions 32 pb + 16 s + {4 h .. 4 h + 3, 8 + 4 h .. 8 + 4 h + 3},
-        // and the V^T operand is read in the same order; P as hi + lo,
-        // hi = bf16(p), lo = bf16(p - hi) (the subtraction is exact)
+        // O^T += V^T P^T, two 16-position K steps per block: step (pb, s)
+        // takes the lane's registers 4 g + r for g = 2 s, 2 s + 1 of block
+        // pb, i.e. positions 32 pb + 16 s + {4 h .. 4 h + 3, 8 + 4 h .. 8 + 4 h + 3},
+        // and the V^T operand is read in the same order
 #pragma unroll
-        for (int pb = 0; pb < 2; ++pb)
+        for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
             for (int sx = 0; sx < 2; ++sx) {
-                const float* pp = &pv[pb * 16 + sx * 8];
-                u32x4_t bh, bl;
+                float* pp = &pv[pb * 16 + sx * 8];
+                u32x4_t bt[kTerms];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t hw = moe::cvt_pk_bf16(pp[2 * i], pp[2 * i + 1]);
-                    bh[i] = hw;
-                    bl[i] = moe::cvt_pk_bf16(pp[2 * i] - __uint_as_float(hw << 16),
-                                             pp[2 * i + 1] - __uint_as_float(hw & 0xFFFF0000u));
-                }
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int q = 0; q < kTerms; ++q) {
+                        const uint32_t hw = moe::cvt_pk_bf16(pp[2 * i], pp[2 * i + 1]);
+                        bt[q][i] = hw;
+                        pp[2 * i] -= __uint_as_float(hw << 16);
+                        pp[2 * i + 1] -= __uint_as_float(hw & 0xFFFF0000u);
+                    }
 #pragma unroll
                 for (int b = 0; b < DB; ++b) {
-                    const uint32_t* vr = vt32 + ((b * 32 + c) * VROW + pb * 32 + sx * 16 + 4 * h) / 2;
+                    const uint32_t* vr = vt32 + ((b * 32 + c) * VROW + (pg * NB + pb) * 32 + sx * 16 + 4 * h) / 2;
                     const uint2 v0 = *reinterpret_cast<const uint2*>(vr);
                     const uint2 v1 = *reinterpret_cast<const uint2*>(vr + 4);
                     const u32x4_t av = {v0.x, v0.y, v1.x, v1.y};
-                    o[b] = mfma32x32x16(av, bh, o[b]);
-                    o[b] = mfma32x32x16(av, bl, o[b]);
+#pragma unroll
+                    for (int q = 0; q < kTerms; ++q) o[b] = mfma32x32x16(av, bt[q], o[b]);
                 }
             }
     }
-    if (!tok_ok) return;
-    // lane: dims 32 b + 8 g + 4 h + r of token t (register 4 g + r)
+    if constexpr (kPG > 1) {
+        // the other position groups' sums, merged in group order by group 0
+        float* mg = reinterpret_cast<float*>(lds);
+        __syncthreads();
+        if (pg > 0) {
+            float* dst = mg + (w - kRowWaves) * (DB * 16 + 2) * 64 + lane;
+#pragma unroll
+            for (int b = 0; b < DB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dst[(b * 16 + i) * 64] = o[b][i];
+            dst[DB * 16 * 64] = m;
+            dst[(DB * 16 + 1) * 64] = l;
+        }
+        __syncthreads();
+        if (pg > 0) return;
+#pragma unroll
+        for (int k = 1; k < kPG; ++k) {
+            const float* src = mg + ((k - 1) * kRowWaves + w) * (DB * 16 + 2) * 64 + lane;
+            const float m2 = src[DB * 16 * 64], l2 = src[(DB * 16 + 1) * 64];
+            const float mn = fmaxf(m, m2);
+            const float f1 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+            const float f2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mn);
+#pragma unroll
+            for (int b = 0; b < DB; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    o[b][i] = fmaf(src[(b * 16 + i) * 64], f2, o[b][i] * f1);
+            l = fmaf(l2, f2, l * f1);
+            m = mn;
+        }
+    }
+    if (!row_ok) return;
+    // lane: dims 32 b + 8 g + 4 h + r of its row (register 4 g + r)
+    if (a.n_split > 1) {
+        float* dst = a.part + (((int64_t)t * a.H + j) * a.n_split + split) * (HD + kPartPad);
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<float4*>(dst + b * 32 + 8 * g + 4 * h) =
+                    make_float4(o[b][4 * g], o[b][4 * g + 1], o[b][4 * g + 2], o[b][4 * g + 3]);
+        if (h == 0) {
+            dst[HD] = m;
+            dst[HD + 1] = l;
+        }
+        return;
+    }
+    // few tokens divide, as merge_kernel does, so that a token's bits do not
+    // depend on whether the positions come in one range or several
     const float inv = 1.0f / l;
+    auto norm = [&](float v) { return kTerms == 3 ? v / l : v * inv; };
     uint16_t* dst = a.out + ((int64_t)t * a.H + j) * HD + 4 * h;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             *reinterpret_cast<uint2*>(dst + b * 32 + 8 * g) =
-                make_uint2(pack_bf16x2(o[b][4 * g] * inv, o[b][4 * g + 1] * inv),
-                           pack_bf16x2(o[b][4 * g + 2] * inv, o[b][4 * g + 3] * inv));
+                make_uint2(pack_bf16x2(norm(o[b][4 * g]), norm(o[b][4 * g + 1])),
+                           pack_bf16x2(norm(o[b][4 * g + 2]), norm(o[b][4 * g + 3])));
+}
+
+// merge_kernel, one workgroup of 4 waves per (token, query head): the
+// position ranges' sums merged by their maxima.  Thread s takes range s's
+// maximum and weight (n_split <= 256); wave w adds the weighted sums of
+// ranges w, w + 4, ... (two dims per lane at head_dim 128, one at 64), the
+// four waves' sums are added in wave order.
+struct MergeArgs {
+    const float* part;
+    uint16_t* out;         // [T][H * hd] bf16
+    int n_split;
+};
+
+template <int HD>
+__global__ __launch_bounds__(256) void merge_kernel(MergeArgs a)
+{
+    constexpr int D = HD / 64;
+    __shared__ float fs[256], red[2][4], sums[4][HD];
+    const int th = blockIdx.x, S = a.n_split;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const float* base = a.part + (int64_t)th * S * (HD + kPartPad);
+    const float ms = tid < S ? base[(int64_t)tid * (HD + kPartPad) + HD] : -INFINITY;
+    const float ls = tid < S ? base[(int64_t)tid * (HD + kPartPad) + HD + 1] : 0.f;
+    float M = ms;
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+    if (lane == 0) red[0][w] = M;
+    __syncthreads();
+    M = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+    const float f = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);
+    fs[tid] = f;
+    float L = ls * f;
+    for (int off = 32; off >= 1; off >>= 1) L += __shfl_xor(L, off, 64);
+    if (lane == 0) red[1][w] = L;
+    __syncthreads();
+    L = ((red[1][0] + red[1][1]) + red[1][2]) + red[1][3];
+    float acc[D];
+#pragma unroll
+    for (int e = 0; e < D; ++e) acc[e] = 0.f;
+#pragma unroll 8
+    for (int k = w; k < S; k += 4) {
+        const float* pc = base + (int64_t)k * (HD + kPartPad) + lane * D;
+        const float fk = fs[k];
+        if constexpr (D == 2) {
+            const float2 v = *reinterpret_cast<const float2*>(pc);
+            acc[0] = fmaf(v.x, fk, acc[0]);
+            acc[1] = fmaf(v.y, fk, acc[1]);
+        } else {
+            acc[0] = fmaf(pc[0], fk, acc[0]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < D; ++e) sums[w][lane * D + e] = acc[e];
+    __syncthreads();
+    if (tid < HD) {
+        const float v = ((sums[0][tid] + sums[1][tid]) + sums[2][tid]) + sums[3][tid];
+        a.out[(int64_t)th * HD + tid] = moe::f32_to_bf16(v / L);
+    }
+}
+
+// merge_few_kernel: the same for few ranges (n_split <= 64) and many rows,
+// one wave per (token, query head): lane s takes range s's maximum and weight,
+// then every lane adds its dims of the ranges in order.
+template <int HD>
+__global__ __launch_bounds__(256) void merge_few_kernel(MergeArgs a, int n)
+{
+    constexpr int D = HD / 64;
+    const int th = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, S = a.n_split;
+    if (th >= n) return;
+    const float* base = a.part + (int64_t)th * S * (HD + kPartPad);
+    const float ms = lane < S ? base[(int64_t)lane * (HD + kPartPad) + HD] : -INFINITY;
+    const float ls = lane < S ? base[(int64_t)lane * (HD + kPartPad) + HD + 1] : 0.f;
+    float M = ms;
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+    const float f = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);
+    float L = ls * f;
+    for (int off = 32; off >= 1; off >>= 1) L += __shfl_xor(L, off, 64);
+    float acc[D];
+#pragma unroll
+    for (int e = 0; e < D; ++e) acc[e] = 0.f;
+    for (int k = 0; k < S; ++k) {
+        const float* pc = base + (int64_t)k * (HD + kPartPad) + lane * D;
+        const float fk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), k));
+#pragma unroll
+        for (int e = 0; e < D; ++e) acc[e] = fmaf(pc[e], fk, acc[e]);
+    }
+    uint16_t* dst = a.out + (int64_t)th * HD + lane * D;
+    if constexpr (D == 2)
+        *reinterpret_cast<uint32_t*>(dst) = pack_bf16x2(acc[0] / L, acc[1] / L);
+    else
+        dst[0] = moe::f32_to_bf16(acc[0] / L);
 }
 
 // y = bf16(x + o), 8 elements per thread
@@ -1019,23 +1200,6 @@ hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N
     return hipGetLastError();
 }
 
-int attn_chunks(int n_pos) { return (n_pos + attn::kChunk - 1) / attn::kChunk; }
-int attn_part_stride(int hd) { return hd + attn::kPartPad; }
-
-hipError_t attn_launch_score(const uint16_t* q, const uint16_t* kc, const uint16_t* vc,
-                             float* part, int T, int H, int G, int hd, int max_seq, int pos0,
-                             int n_chunks_alloc, hipStream_t s)
-{
-    const int n_chunks = attn_chunks(pos0 + T);
-    attn::ScoreArgs a{q, kc, vc, part, T, H, G, max_seq, pos0, n_chunks_alloc,
-                      (float)(1.0 / sqrt((double)hd))};
-    if (hd == 128)
-        hipLaunchKernelGGL(attn::score_kernel<128>, dim3(G, n_chunks), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(attn::score_kernel<64>, dim3(G, n_chunks), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
 hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qkv, uint16_t* q,
                             uint16_t* kc, uint16_t* vc, int T, int H, int G, int hd, int max_seq,
                             int pos0, int n_split, hipStream_t s)
@@ -1045,18 +1209,128 @@ hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qk
     return hipGetLastError();
 }
 
-hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16_t* vc,
+int attn_part_stride(int hd) { return hd + attn::kPartPad; }
+
+// Whether score_kernel and combine_kernel take the call: up to 16 query rows
+// per key/value head and 1024 positions, where one step's fixed latency
+// decides (one token, DBRX block, against flash_kernel: after 100 positions
+// 42.0 us per block against 45.6, 500 42.1 against 44.1, 1000 43.5 against
+// 43.4, 2047 45.4 against 43.7).  At most kShortChunks chunks.
+constexpr int kShortPos = 1024;
+constexpr int kShortChunks = kShortPos / attn::kChunk;
+
+int attn_short(int T, int H, int G, int n_pos) { return T * (H / G) <= 16 && n_pos <= kShortPos; }
+
+// Position groups of flash_kernel's workgroups: 64 or 128 query rows (for up
+// to 32 rows, four groups of 32-row workgroups measured slower: one token
+// after 2047 positions 46.3 us per block against 43.7, after 16000 56.7
+// against 54.8).
+static int flash_pg(int T, int H, int G)
+{
+    const int R = T * (H / G);
+    return R <= 64 ? 2 : 1;
+}
+
+// The most position ranges for T new tokens, whatever their positions: at
+// most 1024 workgroups, 2^17 rows of partial sums (69 MB at head_dim 128) and
+// 128 ranges.
+int attn_split_max(int T, int H, int G)
+{
+    const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg);
+    const int64_t blocks = (int64_t)G * (((int64_t)T * (H / G) + rows - 1) / rows);
+    return (int)std::max<int64_t>(attn_short(T, H, G, 1) ? kShortChunks : 1,
+                                  std::min<int64_t>({1024 / blocks, (1 << 17) / ((int64_t)T * H), 128}));
+}
+
+// Position ranges for T new tokens at pos0: the count with the least
+// estimated time, in steps of one workgroup (about 2.8 us with two per CU).
+// A workgroup costs its steps and about two more; 512 run at a time, in
+// rounds that are cut short as far as the row blocks differ in length; the
+// partial sums are written and read at about 5 TB/s.  Measured (DBRX block,
+// whole call, one range -> the chosen count): 16 tokens after 16000 positions
+// 219 -> 88 us (64 ranges; 32: 89, 128: 103), 64 after 8000 426 -> 123 (32;
+// 16: 134, 64: 141), 300 after 1000 189 -> 161 (4; 2: 168, 8: 169), 512 after
+// 8000 528 -> 367 (5; 2: 385); 1024 from empty 306 (1; 2: 339).
+int attn_split(int T, int H, int G, int pos0)
+{
+    const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg), step = attn::kFlashP;
+    const int64_t nrb = ((int64_t)T * (H / G) + rows - 1) / rows;
+    const double longest = (double)((pos0 + T + step - 1) / step), shortest = (double)(pos0 / step + 1);
+    const int64_t most = std::min<int64_t>(attn_split_max(T, H, G), (int64_t)longest);
+    int best = 1;
+    double best_cost = 0.0;
+    for (int S = 1; S <= most; ++S) {
+        const double n = (double)G * nrb * S, full = n / 512.0;
+        const double longest_s = std::ceil(longest / S) + 2.0, shortest_s = std::ceil(shortest / S) + 2.0;
+        double cost = std::max(longest_s, full * 0.5 * (longest_s + shortest_s) +
+                                              (std::ceil(full) - full) * shortest_s);
+        if (S > 1) cost += (double)T * H * S * 8e-5 + 1.5;
+        if (S == 1 || cost < 0.98 * best_cost) { best = S; best_cost = cost; }
+    }
+    return best;
+}
+
+hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, float* part,
                              uint16_t* out, int T, int H, int G, int hd, int max_seq, int pos0,
+                             int few, int n_split, hipStream_t s)
+{
+    const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg);
+    const int nrb = (T * (H / G) + rows - 1) / rows;
+    attn::FlashArgs a{q, kc, vc, out, part, T, H, G, max_seq, pos0, nrb, n_split,
+                      (float)(1.4426950408889634 / sqrt((double)hd))};
+    const dim3 grid((G * nrb * n_split + attn::kXcds - 1) / attn::kXcds * attn::kXcds), block(256);
+#define ATTN_FLASH(HD, PG) \
+    hipLaunchKernelGGL((few ? attn::flash_kernel<HD, PG, 3> : attn::flash_kernel<HD, PG, 2>), grid, block, 0, s, a)
+    if (hd == 128) {
+        if (pg == 2) ATTN_FLASH(128, 2);
+        else ATTN_FLASH(128, 1);
+    } else {
+        if (pg == 2) ATTN_FLASH(64, 2);
+        else ATTN_FLASH(64, 1);
+    }
+#undef ATTN_FLASH
+    return hipGetLastError();
+}
+
+hipError_t attn_launch_short(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, float* part,
+                             int T, int H, int G, int hd, int max_seq, int pos0, hipStream_t s)
+{
+    const int n_chunks = (pos0 + T + attn::kChunk - 1) / attn::kChunk;
+    attn::ScoreArgs a{q, kc, vc, part, T, H, G, max_seq, pos0, n_chunks,
+                      (float)(1.0 / sqrt((double)hd))};
+    if (hd == 128)
+        hipLaunchKernelGGL(attn::score_kernel<128>, dim3(G, n_chunks), dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL(attn::score_kernel<64>, dim3(G, n_chunks), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t attn_launch_short_merge(const float* part, uint16_t* out, int T, int H, int hd, int pos0,
+                                   hipStream_t s)
+{
+    attn::CombineArgs c{part, out, H, hd, pos0, (pos0 + T + attn::kChunk - 1) / attn::kChunk};
+    hipLaunchKernelGGL(attn::combine_kernel, dim3(T * H), dim3(128), 0, s, c);
+    return hipGetLastError();
+}
+
+hipError_t attn_launch_merge(const float* part, uint16_t* out, int T, int H, int hd, int n_split,
                              hipStream_t s)
 {
-    const int nqb = (T + attn::kFlashQ - 1) / attn::kFlashQ;
-    attn::FlashArgs a{q, kc, vc, out, T, H, G, max_seq, pos0, nqb,
-                      (float)(1.4426950408889634 / sqrt((double)hd))};
-    const dim3 grid((H * nqb + attn::kXcds - 1) / attn::kXcds * attn::kXcds);
-    if (hd == 128)
-        hipLaunchKernelGGL(attn::flash_kernel<128>, grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(attn::flash_kernel<64>, grid, dim3(256), 0, s, a);
+    attn::MergeArgs a{part, out, n_split};
+    const int n = T * H;
+    // many rows of few ranges: a wave each (300 tokens of 48 heads, 4 ranges:
+    // 15.9 -> 9 us); few rows: a workgroup each (48 rows of 8 ranges: 3.5 us
+    // against 5.0)
+    if (n >= 2048 && n_split <= 16) {
+        if (hd == 128)
+            hipLaunchKernelGGL(attn::merge_few_kernel<128>, dim3((n + 3) / 4), dim3(256), 0, s, a, n);
+        else
+            hipLaunchKernelGGL(attn::merge_few_kernel<64>, dim3((n + 3) / 4), dim3(256), 0, s, a, n);
+    } else if (hd == 128) {
+        hipLaunchKernelGGL(attn::merge_kernel<128>, dim3(n), dim3(256), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(attn::merge_kernel<64>, dim3(n), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
@@ -1066,14 +1340,6 @@ hipError_t attn_launch_residual(const uint16_t* x, float* o, const float* op, in
     const int64_t n8 = n / 8;
     hipLaunchKernelGGL(attn::residual_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s,
                        x, o, op, n_split, y, n8);
-    return hipGetLastError();
-}
-
-hipError_t attn_launch_combine(const float* part, uint16_t* out, int T, int H, int hd, int pos0,
-                               int n_chunks_alloc, hipStream_t s)
-{
-    attn::CombineArgs c{part, out, H, hd, pos0, n_chunks_alloc};
-    hipLaunchKernelGGL(attn::combine_kernel, dim3(T * H), dim3(128), 0, s, c);
     return hipGetLastError();
 }
 

@@ -34,7 +34,7 @@ struct Layout {
         arena_bytes;
     size_t cache_head_elems, cache_layer_bytes, cache_bytes;
     size_t h_off, qkv_off, q_off, part_off, a_off, o_off, qkvp_off, ws_bytes;
-    int nqkv, nq, n_chunks;
+    int nqkv, nq;
 };
 
 const char* check_config(const attn_config* c)
@@ -79,15 +79,19 @@ Layout make_layout(const attn_config* c)
     L.cache_head_elems = (size_t)c->max_seq * hd;
     L.cache_layer_bytes = 2 * G * L.cache_head_elems * 2;
     L.cache_bytes = L.cache_layer_bytes * c->n_layers;
-    L.n_chunks = attn_chunks(c->max_seq);
     const size_t Tm = c->max_tokens;
-    const size_t Td = std::min<size_t>(Tm, kDecodeTokens);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
     L.h_off = take(Tm * d * 2);
     L.qkv_off = take(Tm * L.nqkv * 4);
     L.q_off = take(Tm * L.nq * 2);
-    L.part_off = take(Td * H * L.n_chunks * attn_part_stride((int)hd) * 4);
+    // the attention's partial sums over position ranges (none with one range)
+    size_t part_rows = 0;
+    for (int T = 1; T <= (int)Tm; ++T) {
+        const int n_split = attn_split_max(T, c->n_heads, c->n_kv_heads);
+        if (n_split > 1) part_rows = std::max(part_rows, (size_t)T * H * n_split);
+    }
+    L.part_off = take(part_rows * attn_part_stride((int)hd) * 4);
     L.a_off = take(Tm * L.nq * 2);
     L.o_off = take(Tm * d * 4);
     if (Tm > (size_t)kDecodeTokens) {
@@ -190,6 +194,41 @@ hipError_t project(const uint8_t* wpk, const uint16_t* in, int K, int N, float* 
     return moe_launch_gemm_down(&g, s);
 }
 
+// Causal attention of the T rotated query rows q into a (bf16), over one or
+// several position ranges; few: a call of
+// the decode path (T <= 16).
+moe_status attention(attn_ctx* ctx, int layer, const uint16_t* q, uint16_t* a, int T, int pos0,
+                     int few, hipStream_t s)
+{
+    const attn_config& c = ctx->cfg;
+    float* part = reinterpret_cast<float*>(ctx->ws + ctx->L.part_off);
+    hipError_t e;
+    if (few && attn_short(T, c.n_heads, c.n_kv_heads, pos0 + T)) {
+        e = timed(ctx, ATTN_K_SCORE, s, [&] {
+            return attn_launch_short(q, layer_k(ctx, layer), layer_v(ctx, layer), part, T, c.n_heads,
+                                     c.n_kv_heads, c.head_dim, c.max_seq, pos0, s);
+        });
+        if (e != hipSuccess) return hip_fail(ctx, e, "attention kernel launch");
+        e = timed(ctx, ATTN_K_COMBINE, s, [&] {
+            return attn_launch_short_merge(part, a, T, c.n_heads, c.head_dim, pos0, s);
+        });
+        if (e != hipSuccess) return hip_fail(ctx, e, "merge kernel launch");
+        return MOE_OK;
+    }
+    const int n_split = attn_split(T, c.n_heads, c.n_kv_heads, pos0);   // at most attn_split_max
+    e = timed(ctx, ATTN_K_SCORE, s, [&] {
+        return attn_launch_flash(q, layer_k(ctx, layer), layer_v(ctx, layer), part, a, T, c.n_heads,
+                                 c.n_kv_heads, c.head_dim, c.max_seq, pos0, few, n_split, s);
+    });
+    if (e != hipSuccess) return hip_fail(ctx, e, "attention kernel launch");
+    if (n_split == 1) return MOE_OK;
+    e = timed(ctx, ATTN_K_COMBINE, s, [&] {
+        return attn_launch_merge(part, a, T, c.n_heads, c.head_dim, n_split, s);
+    });
+    if (e != hipSuccess) return hip_fail(ctx, e, "merge kernel launch");
+    return MOE_OK;
+}
+
 // The block for T > 16 new tokens: norm -> q|k|v (GEMM) -> rotation and
 // cache append -> causal attention -> o = a Wo (GEMM) -> residual.
 moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int T, int pos0,
@@ -205,6 +244,7 @@ moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int
     uint16_t* a = reinterpret_cast<uint16_t*>(ctx->ws + L.a_off);
     float* o = reinterpret_cast<float*>(ctx->ws + L.o_off);
     const int d = c.d_model;
+    moe_status st;
     const int sq = moe_gemm_plain_split(T, L.nqkv), so = moe_gemm_plain_split(T, d);
     const float* gamma = reinterpret_cast<const float*>(w);
     hipError_t e = timed(ctx, ATTN_K_NORM, s, [&] {
@@ -219,11 +259,8 @@ moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int
                                 c.n_kv_heads, c.head_dim, c.max_seq, pos0, sq, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "rotation kernel launch");
-    e = timed(ctx, ATTN_K_SCORE, s, [&] {
-        return attn_launch_flash(q, layer_k(ctx, layer), layer_v(ctx, layer), a, T, c.n_heads,
-                                 c.n_kv_heads, c.head_dim, c.max_seq, pos0, s);
-    });
-    if (e != hipSuccess) return hip_fail(ctx, e, "attention kernel launch");
+    st = attention(ctx, layer, q, a, T, pos0, 0, s);
+    if (st != MOE_OK) return st;
     e = timed(ctx, ATTN_K_OUT, s, [&] { return project(w + L.wo_off, a, L.nq, d, so > 1 ? qkvp : o, T, so, s); });
     if (e != hipSuccess) return hip_fail(ctx, e, "output projection GEMM launch");
     e = timed(ctx, ATTN_K_RESIDUAL, s, [&] {
@@ -261,7 +298,6 @@ moe_status forward_impl(attn_ctx* ctx, int32_t layer, const uint16_t* x, uint16_
     uint16_t* h = reinterpret_cast<uint16_t*>(ctx->ws + L.h_off);
     float* qkv = reinterpret_cast<float*>(ctx->ws + L.qkv_off);
     uint16_t* q = reinterpret_cast<uint16_t*>(ctx->ws + L.q_off);
-    float* part = reinterpret_cast<float*>(ctx->ws + L.part_off);
     uint16_t* a = reinterpret_cast<uint16_t*>(ctx->ws + L.a_off);
     float* o = reinterpret_cast<float*>(ctx->ws + L.o_off);
     const int d = c.d_model;
@@ -281,15 +317,8 @@ moe_status forward_impl(attn_ctx* ctx, int32_t layer, const uint16_t* x, uint16_
                                c.n_kv_heads, c.head_dim, c.max_seq, pos0, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "projection kernel launch");
-    e = timed(ctx, ATTN_K_SCORE, s, [&] {
-        return attn_launch_score(q, layer_k(ctx, layer), layer_v(ctx, layer), part, T, c.n_heads,
-                                 c.n_kv_heads, c.head_dim, c.max_seq, pos0, L.n_chunks, s);
-    });
-    if (e != hipSuccess) return hip_fail(ctx, e, "attention kernel launch");
-    e = timed(ctx, ATTN_K_COMBINE, s, [&] {
-        return attn_launch_combine(part, a, T, c.n_heads, c.head_dim, pos0, L.n_chunks, s);
-    });
-    if (e != hipSuccess) return hip_fail(ctx, e, "merge kernel launch");
+    const moe_status st = attention(ctx, layer, q, a, T, pos0, 1, s);
+    if (st != MOE_OK) return st;
     e = timed(ctx, ATTN_K_OUT, s, [&] {
         return attn_launch_out(w + L.wo_off, a, T, L.nq, d, o, x, y, s);
     });

@@ -188,16 +188,19 @@ hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N
 hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qkv, uint16_t* q,
                             uint16_t* kc, uint16_t* vc, int T, int H, int G, int hd, int max_seq,
                             int pos0, int n_split, hipStream_t s);
-hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16_t* vc,
+int attn_part_stride(int hd);
+int attn_short(int T, int H, int G, int n_pos);
+hipError_t attn_launch_short(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, float* part,
+                             int T, int H, int G, int hd, int max_seq, int pos0, hipStream_t s);
+hipError_t attn_launch_short_merge(const float* part, uint16_t* out, int T, int H, int hd, int pos0,
+                                   hipStream_t s);
+int attn_split_max(int T, int H, int G);
+int attn_split(int T, int H, int G, int pos0);
+hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, float* part,
                              uint16_t* out, int T, int H, int G, int hd, int max_seq, int pos0,
+                             int few, int n_split, hipStream_t s);
+hipError_t attn_launch_merge(const float* part, uint16_t* out, int T, int H, int hd, int n_split,
                              hipStream_t s);
 hipError_t attn_launch_residual(const uint16_t* x, float* o, const float* op, int n_split, uint16_t* y, int64_t n,
                                 hipStream_t s);
-int attn_chunks(int n_pos);
-int attn_part_stride(int hd);
-hipError_t attn_launch_score(const uint16_t* q, const uint16_t* kc, const uint16_t* vc,
-                             float* part, int T, int H, int G, int hd, int max_seq, int pos0,
-                             int n_chunks_alloc, hipStream_t s);
-hipError_t attn_launch_combine(const float* part, uint16_t* out, int T, int H, int hd, int pos0,
-                               int n_chunks_alloc, hipStream_t s);
 }

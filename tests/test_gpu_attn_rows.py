@@ -1,0 +1,39 @@
+"""The attention kernels at the edges of their row blocks, position steps and
+position ranges, every stage per element against the oracle (the bounds of
+test_gpu_attn.check_block).
+
+The rows of one key/value head are the (token, query head of its group)
+pairs: up to 16 rows and 1024 positions take score_kernel, otherwise
+flash_kernel in blocks of 64 (up to 64 rows) or 128 rows and steps of 64
+positions, in one or several ranges."""
+import pytest
+
+from test_gpu_attn import TINY, Case, check_block, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,G,hd,T,pos0", [
+    (16, 2, 64, 2, 1022),      # 16 rows, 1024 positions: the last of score_kernel
+    (16, 2, 64, 2, 1023),      # 1025 positions: flash_kernel, the last step one position
+    (8, 4, 128, 9, 0),         # 18 rows, one step, one range
+    (16, 2, 64, 4, 60),        # 32 rows, positions across a step
+    (12, 2, 128, 11, 1500),    # 66 rows: the first size of 128-row blocks
+    (16, 2, 64, 8, 2000),      # 64 rows, as many ranges as steps
+    (16, 2, 128, 16, 3000),    # 128 rows, the most of the decode path
+    (4, 4, 64, 33, 63),        # prefill, one head per group: rows are tokens
+    (4, 4, 64, 65, 2000),      # 65 rows: a second wave with one row
+    (8, 1, 128, 17, 3500),     # 136 rows over one key/value head: two blocks, many ranges
+    (8, 1, 128, 48, 1000),     # 384 rows: whole blocks
+])
+def test_row_and_range_edges(torch_mod, H, G, hd, T, pos0):  # noqa: F811
+    wl = TINY.with_(d=512, n_heads=H, n_kv=G, hd=hd, T=T, pos0=pos0, max_seq=4096)
+    case = Case(torch_mod, wl, max_tokens=max(T, 16))
+    try:
+        x = wl.x()
+        y = case.forward(x, pos0)
+        kc, vc = case.cache()
+        check_block(case, x, pos0, y, case.layer.intermediates(T), kc, vc)
+        assert (case.forward(x, pos0) == y).all()
+    finally:
+        case.close()
