@@ -149,6 +149,20 @@ __global__ __launch_bounds__(64 * kSplit) void gemv_kernel(GemvArgs a)
     *reinterpret_cast<uint2*>(a.y16 + o) = make_uint2(lo, hi);
 }
 
+// cos and sin of pos * inv_freq: the angle is formed and reduced modulo 2 pi
+// in fp64 (2 pi split in two parts, Cody and Waite), so sincosf only sees an
+// argument within [-pi, pi]
+__device__ inline void rope_cs(int pos, double inv_freq, float& c, float& s)
+{
+    constexpr double kTwoPiHi = 6.28318530717958623200e+00;   // 2 pi rounded to fp64
+    constexpr double kTwoPiLo = 2.44929359829470635445e-16;   // 2 pi - kTwoPiHi
+    constexpr double kInvTwoPi = 1.59154943091895335769e-01;
+    const double ang = (double)pos * inv_freq;
+    const double k = rint(ang * kInvTwoPi);
+    const double r = fma(-k, kTwoPiLo, fma(-k, kTwoPiHi, ang));
+    sincosf((float)r, &s, &c);
+}
+
 // Layer norm, one workgroup of 256 threads per token: the thread's 8-element
 // groups of x are loaded once into registers, x and x^2 summed in fp64 (so
 // E[x^2] - mean^2 loses nothing), a butterfly per wave and the 4 wave sums in
@@ -159,7 +173,10 @@ constexpr int kNormGroups = 4;     // 8-element groups per thread (d <= 8192)
 __global__ __launch_bounds__(kNormThreads) void norm_kernel(const uint16_t* __restrict__ x,
                                                             const float* __restrict__ gamma,
                                                             int d, float eps,
-                                                            uint16_t* __restrict__ h)
+                                                            uint16_t* __restrict__ h,
+                                                            const double* __restrict__ inv_freq,
+                                                            float* __restrict__ cos_sin, int hd,
+                                                            int pos0)
 {
     __shared__ double red[2][kNormThreads / 64];
     const int t = blockIdx.x;
@@ -207,6 +224,13 @@ __global__ __launch_bounds__(kNormThreads) void norm_kernel(const uint16_t* __re
         }
         *reinterpret_cast<u32x4_t*>(h + (int64_t)t * d + e * 8) = out;
     }
+    // prefill: the token's rotation, cos and sin of its position times every
+    // frequency (formed once here instead of once per head)
+    if (cos_sin && (int)threadIdx.x < hd / 2) {
+        float c, s;
+        rope_cs(pos0 + t, inv_freq[threadIdx.x], c, s);
+        *reinterpret_cast<float2*>(cos_sin + ((int64_t)t * (hd / 2) + threadIdx.x) * 2) = make_float2(c, s);
+    }
 }
 
 // The fused projection q|k|v = h Wqkv, one workgroup per 16 packed rows (8
@@ -231,20 +255,6 @@ struct QkvArgs {
     uint16_t* vc;          // this layer's V cache
     int d, T, H, G, hd, max_seq, pos0;
 };
-
-// cos and sin of pos * inv_freq: the angle is formed and reduced modulo 2 pi
-// in fp64 (2 pi split in two parts, Cody and Waite), so sincosf only sees an
-// argument within [-pi, pi]
-__device__ inline void rope_cs(int pos, double inv_freq, float& c, float& s)
-{
-    constexpr double kTwoPiHi = 6.28318530717958623200e+00;   // 2 pi rounded to fp64
-    constexpr double kTwoPiLo = 2.44929359829470635445e-16;   // 2 pi - kTwoPiHi
-    constexpr double kInvTwoPi = 1.59154943091895335769e-01;
-    const double ang = (double)pos * inv_freq;
-    const double k = rint(ang * kInvTwoPi);
-    const double r = fma(-k, kTwoPiLo, fma(-k, kTwoPiHi, ang));
-    sincosf((float)r, &s, &c);
-}
 
 // barrier for LDS traffic only: waits for this wave's LDS operations, not
 // for its outstanding global loads (the weight batch in flight)
@@ -653,54 +663,69 @@ __global__ __launch_bounds__(128) void combine_kernel(CombineArgs a)
 // More than 16 new tokens: the projections run on the grouped GEMM of
 // moe_prefill.hip (one "expert", its rows the tokens), then these kernels.
 
-// rope_kernel, one workgroup per token: from the projection's fp32 output
-// in packed row order (query and key features placed by rope_row), the
+// rope_kernel, where the projection's reduction was split (otherwise its
+// epilogue does this): the partial sums, [n_split][T][nqkv] fp32 in packed
+// row order (query and key features placed by rope_row), added in order; the
 // natural-order fp32 q|k|v (kept for inspection), q rotated to bf16 in the
-// workspace, k rotated and v to the cache at position pos0 + t.  The angle
-// and rotation arithmetic are the decode epilogue's (rope_cs).
+// workspace, k rotated and v to the cache at position pos0 + t.  A thread
+// takes four rotation pairs, or eight value features; a workgroup one token's
+// share of blockDim.x such pieces.
 struct RopeArgs {
-    const float* qkvp;     // [T][nqkv] fp32, packed row order
-    const double* inv_freq;
+    const float* qkvp;
+    const float* cos_sin;  // [T][hd/2][2]
     float* qkv;            // [T][nqkv] fp32, natural order
     uint16_t* q;           // [T][H][hd]
     uint16_t* kc;
     uint16_t* vc;
-    int T, H, G, hd, max_seq, pos0;
-    int n_split;           // qkvp is [n_split][T][nqkv] partial sums, added in order
+    int T, H, G, hd, max_seq, pos0, n_split;
 };
+
+__device__ inline uint2 pack_bf16x4(float4 v)
+{
+    return make_uint2((uint32_t)moe::f32_to_bf16(v.x) | ((uint32_t)moe::f32_to_bf16(v.y) << 16),
+                      (uint32_t)moe::f32_to_bf16(v.z) | ((uint32_t)moe::f32_to_bf16(v.w) << 16));
+}
 
 __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a)
 {
-    const int t = blockIdx.x;
-    const int hd = a.hd, half = hd / 2;
+    const int t = blockIdx.x, hd = a.hd, half = hd / 2;
     const int nqk = (a.H + a.G) * hd, nqkv = nqk + a.G * hd;
-    const int pos = a.pos0 + t;
-    const float* src = a.qkvp + (int64_t)t * nqkv;
+    const int e = blockIdx.y * 256 + threadIdx.x;       // 8 consecutive packed features
+    if (e >= nqkv / 8) return;
     const int64_t part = (int64_t)a.T * nqkv;
-    auto load = [&](int i) {
-        float v = src[i];
-        for (int k = 1; k < a.n_split; ++k) v += src[k * part + i];
-        return v;
-    };
-    float* nat = a.qkv + (int64_t)t * nqkv;
-    for (int e = threadIdx.x; e < (a.H + a.G) * half; e += blockDim.x) {
-        const int head = e / half, f = e % half;
-        const int n0 = head * hd + f, n1 = n0 + half;
-        const float x0 = load(moe::rope_row(n0, hd)), x1 = load(moe::rope_row(n1, hd));
-        nat[n0] = x0;
-        nat[n1] = x1;
-        float c, sf;
-        rope_cs(pos, a.inv_freq[f], c, sf);
-        const float r0 = x0 * c - x1 * sf, r1 = x1 * c + x0 * sf;
-        uint16_t* dst = head < a.H ? a.q + ((int64_t)t * a.H + head) * hd
-                                   : a.kc + ((int64_t)(head - a.H) * a.max_seq + pos) * hd;
-        dst[f] = moe::f32_to_bf16(r0);
-        dst[f + half] = moe::f32_to_bf16(r1);
+    const int64_t pos = a.pos0 + t;
+    // packed features of a 16-row tile: 4 u .. + 3 and 8 + 4 u .. + 3 (u = e % 2)
+    const float* src = a.qkvp + (int64_t)t * nqkv + e / 2 * 16 + e % 2 * 4;
+    float4 x0 = *reinterpret_cast<const float4*>(src), x1 = *reinterpret_cast<const float4*>(src + 8);
+    for (int k = 1; k < a.n_split; ++k) {
+        const float4 p0 = *reinterpret_cast<const float4*>(src + k * part);
+        const float4 p1 = *reinterpret_cast<const float4*>(src + k * part + 8);
+        x0.x += p0.x; x0.y += p0.y; x0.z += p0.z; x0.w += p0.w;
+        x1.x += p1.x; x1.y += p1.y; x1.z += p1.z; x1.w += p1.w;
     }
-    for (int e = threadIdx.x; e < a.G * hd; e += blockDim.x) {
-        const float v = load(nqk + e);
-        nat[nqk + e] = v;
-        a.vc[((int64_t)(e / hd) * a.max_seq + pos) * hd + e % hd] = moe::f32_to_bf16(v);
+    float* nat = a.qkv + (int64_t)t * nqkv;
+    const int n0 = e / 2 * 16;
+    if (n0 < nqk) {
+        const int head = n0 / hd, f0 = n0 % hd / 2 + e % 2 * 4;
+        const float* cs = a.cos_sin + ((int64_t)t * half + f0) * 2;
+        const float4 c01 = *reinterpret_cast<const float4*>(cs), c23 = *reinterpret_cast<const float4*>(cs + 4);
+        const float4 r0 = make_float4(x0.x * c01.x - x1.x * c01.y, x0.y * c01.z - x1.y * c01.w,
+                                      x0.z * c23.x - x1.z * c23.y, x0.w * c23.z - x1.w * c23.w);
+        const float4 r1 = make_float4(x1.x * c01.x + x0.x * c01.y, x1.y * c01.z + x0.y * c01.w,
+                                      x1.z * c23.x + x0.z * c23.y, x1.w * c23.z + x0.w * c23.w);
+        *reinterpret_cast<float4*>(nat + head * hd + f0) = x0;
+        *reinterpret_cast<float4*>(nat + head * hd + f0 + half) = x1;
+        uint16_t* dst = (head < a.H ? a.q + ((int64_t)t * a.H + head) * hd
+                                    : a.kc + ((int64_t)(head - a.H) * a.max_seq + pos) * hd) + f0;
+        *reinterpret_cast<uint2*>(dst) = pack_bf16x4(r0);
+        *reinterpret_cast<uint2*>(dst + half) = pack_bf16x4(r1);
+    } else {
+        const int n = n0 + e % 2 * 4;
+        *reinterpret_cast<float4*>(nat + n) = x0;
+        *reinterpret_cast<float4*>(nat + n + 8) = x1;
+        uint16_t* dst = a.vc + ((int64_t)((n0 - nqk) / hd) * a.max_seq + pos) * hd + (n - nqk) % hd;
+        *reinterpret_cast<uint2*>(dst) = pack_bf16x4(x0);
+        *reinterpret_cast<uint2*>(dst + 8) = pack_bf16x4(x1);
     }
 }
 
@@ -1126,31 +1151,26 @@ __global__ __launch_bounds__(256) void merge_few_kernel(MergeArgs a, int n)
         dst[0] = moe::f32_to_bf16(acc[0] / L);
 }
 
-// y = bf16(x + o), 8 elements per thread
+// Where the output projection's reduction was split: o = the partial sums
+// [n_split][n] in order, and y = bf16(x + o); 8 elements per thread.
 __global__ __launch_bounds__(256) void residual_kernel(const uint16_t* __restrict__ x,
-                                                       float* o, const float* op, int n_split,
-                                                       uint16_t* y, int64_t n8)
+                                                       const float* __restrict__ op, int n_split,
+                                                       float* __restrict__ o, uint16_t* y, int64_t n8)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n8) return;
     const u32x4_t xv = ld16(x + i * 8);
-    float4 o0, o1;
-    if (n_split > 1) {
-        o0 = *reinterpret_cast<const float4*>(op + i * 8);
-        o1 = *reinterpret_cast<const float4*>(op + i * 8 + 4);
-        for (int k = 1; k < n_split; ++k) {
-            const float* pk = op + (k * n8 + i) * 8;
-            const float4 p0 = *reinterpret_cast<const float4*>(pk);
-            const float4 p1 = *reinterpret_cast<const float4*>(pk + 4);
-            o0.x += p0.x; o0.y += p0.y; o0.z += p0.z; o0.w += p0.w;
-            o1.x += p1.x; o1.y += p1.y; o1.z += p1.z; o1.w += p1.w;
-        }
-        *reinterpret_cast<float4*>(o + i * 8) = o0;
-        *reinterpret_cast<float4*>(o + i * 8 + 4) = o1;
-    } else {
-        o0 = *reinterpret_cast<const float4*>(o + i * 8);
-        o1 = *reinterpret_cast<const float4*>(o + i * 8 + 4);
+    float4 o0 = *reinterpret_cast<const float4*>(op + i * 8);
+    float4 o1 = *reinterpret_cast<const float4*>(op + i * 8 + 4);
+    for (int k = 1; k < n_split; ++k) {
+        const float* pk = op + (k * n8 + i) * 8;
+        const float4 p0 = *reinterpret_cast<const float4*>(pk);
+        const float4 p1 = *reinterpret_cast<const float4*>(pk + 4);
+        o0.x += p0.x; o0.y += p0.y; o0.z += p0.z; o0.w += p0.w;
+        o1.x += p1.x; o1.y += p1.y; o1.z += p1.z; o1.w += p1.w;
     }
+    *reinterpret_cast<float4*>(o + i * 8) = o0;
+    *reinterpret_cast<float4*>(o + i * 8 + 4) = o1;
     const float ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
     u32x4_t out;
 #pragma unroll
@@ -1165,10 +1185,11 @@ __global__ __launch_bounds__(256) void residual_kernel(const uint16_t* __restric
 extern "C" {
 
 hipError_t attn_launch_norm(const uint16_t* x, const float* gamma, int T, int d, float eps,
-                            uint16_t* h, hipStream_t s)
+                            uint16_t* h, const double* inv_freq, float* cos_sin, int hd, int pos0,
+                            hipStream_t s)
 {
     hipLaunchKernelGGL(attn::norm_kernel, dim3(T), dim3(attn::kNormThreads), 0, s, x, gamma, d,
-                       eps, h);
+                       eps, h, inv_freq, cos_sin, hd, pos0);
     return hipGetLastError();
 }
 
@@ -1200,12 +1221,13 @@ hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N
     return hipGetLastError();
 }
 
-hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qkv, uint16_t* q,
+hipError_t attn_launch_rope(const float* qkvp, const float* cos_sin, float* qkv, uint16_t* q,
                             uint16_t* kc, uint16_t* vc, int T, int H, int G, int hd, int max_seq,
                             int pos0, int n_split, hipStream_t s)
 {
-    attn::RopeArgs a{qkvp, inv_freq, qkv, q, kc, vc, T, H, G, hd, max_seq, pos0, n_split};
-    hipLaunchKernelGGL(attn::rope_kernel, dim3(T), dim3(256), 0, s, a);
+    attn::RopeArgs a{qkvp, cos_sin, qkv, q, kc, vc, T, H, G, hd, max_seq, pos0, n_split};
+    const int pieces = (H + 2 * G) * hd / 8;
+    hipLaunchKernelGGL(attn::rope_kernel, dim3(T, (pieces + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1334,12 +1356,12 @@ hipError_t attn_launch_merge(const float* part, uint16_t* out, int T, int H, int
     return hipGetLastError();
 }
 
-hipError_t attn_launch_residual(const uint16_t* x, float* o, const float* op, int n_split,
-                                uint16_t* y, int64_t n, hipStream_t s)
+hipError_t attn_launch_residual(const uint16_t* x, const float* op, int n_split, float* o, uint16_t* y,
+                                int64_t n, hipStream_t s)
 {
     const int64_t n8 = n / 8;
     hipLaunchKernelGGL(attn::residual_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s,
-                       x, o, op, n_split, y, n8);
+                       x, op, n_split, o, y, n8);
     return hipGetLastError();
 }
 

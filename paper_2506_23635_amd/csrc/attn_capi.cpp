@@ -33,7 +33,7 @@ struct Layout {
     size_t gamma_bytes, freq_off, gamma2_off, wqkv_off, wqkv_bytes, wo_off, wo_bytes, layer_bytes,
         arena_bytes;
     size_t cache_head_elems, cache_layer_bytes, cache_bytes;
-    size_t h_off, qkv_off, q_off, part_off, a_off, o_off, qkvp_off, ws_bytes;
+    size_t h_off, qkv_off, q_off, part_off, a_off, o_off, split_off, cs_off, ws_bytes;
     int nqkv, nq;
 };
 
@@ -95,15 +95,16 @@ Layout make_layout(const attn_config* c)
     L.a_off = take(Tm * L.nq * 2);
     L.o_off = take(Tm * d * 4);
     if (Tm > (size_t)kDecodeTokens) {
-        // the projections' outputs in packed row order, or their partial sums
-        // over ranges of the reduction
-        size_t rows_q = Tm, rows_o = 0;
+        // the products' partial sums over ranges of the reduction, and the
+        // tokens' rotations
+        size_t split_elems = 0;
         for (int T = 1; T <= (int)Tm; ++T) {
-            const int so = moe_gemm_plain_split(T, (int)d);
-            rows_q = std::max(rows_q, (size_t)moe_gemm_plain_split(T, L.nqkv) * T);
-            if (so > 1) rows_o = std::max(rows_o, (size_t)so * T);
+            const size_t sq = moe_gemm_plain_split(T, L.nqkv), so = moe_gemm_plain_split(T, (int)d);
+            if (sq > 1) split_elems = std::max(split_elems, sq * T * L.nqkv);
+            if (so > 1) split_elems = std::max(split_elems, so * T * d);
         }
-        L.qkvp_off = take(std::max(rows_q * L.nqkv, rows_o * d) * 4);
+        L.split_off = take(split_elems * 4);
+        L.cs_off = take(Tm * hd * 4);
     }
     L.ws_bytes = off;
     return L;
@@ -172,11 +173,10 @@ uint16_t* layer_v(attn_ctx* c, int l)
     return layer_k(c, l) + (size_t)c->cfg.n_kv_heads * c->L.cache_head_elems;
 }
 
-// One plain GEMM out = in W^T on the grouped GEMM's down mode: a single
-// "expert" whose rows are the T tokens, its weight the packed N x K matrix;
-// with split > 1 partial sums over `split` ranges of K at out + i T N.
-hipError_t project(const uint8_t* wpk, const uint16_t* in, int K, int N, float* out, int T,
-                   int split, hipStream_t s)
+// One plain product in W^T on the grouped GEMM: a single "expert" whose rows
+// are the T tokens, its weight the packed N x K matrix, its reduction in
+// k_split ranges.
+moe::GemmArgs product(const uint8_t* wpk, const uint16_t* in, int K, int N, float* out, int T, int split)
 {
     moe::GemmArgs g{};
     g.experts = wpk;
@@ -191,7 +191,7 @@ hipError_t project(const uint8_t* wpk, const uint16_t* in, int K, int N, float* 
     g.mid = moe_gemm_mid_tiles(T, 1, 1, 1, N);
     g.k_split = split;
     g.split_stride = (uint64_t)T * N;
-    return moe_launch_gemm_down(&g, s);
+    return g;
 }
 
 // Causal attention of the T rotated query rows q into a (bf16), over one or
@@ -229,8 +229,10 @@ moe_status attention(attn_ctx* ctx, int layer, const uint16_t* q, uint16_t* a, i
     return MOE_OK;
 }
 
-// The block for T > 16 new tokens: norm -> q|k|v (GEMM) -> rotation and
-// cache append -> causal attention -> o = a Wo (GEMM) -> residual.
+// The block for T > 16 new tokens: norm (and the tokens' rotations) -> q|k|v
+// with rotation and cache append (GEMM) -> causal attention -> o = a Wo and
+// y (GEMM); where a product's reduction is split, its end is a kernel of its
+// own (few tokens).
 moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int T, int pos0,
                    hipStream_t s)
 {
@@ -239,34 +241,51 @@ moe_status prefill(attn_ctx* ctx, int layer, const uint16_t* x, uint16_t* y, int
     uint8_t* w = layer_w(ctx, layer);
     uint16_t* h = reinterpret_cast<uint16_t*>(ctx->ws + L.h_off);
     float* qkv = reinterpret_cast<float*>(ctx->ws + L.qkv_off);
-    float* qkvp = reinterpret_cast<float*>(ctx->ws + L.qkvp_off);
+    float* part = reinterpret_cast<float*>(ctx->ws + L.split_off);
+    float* cs = reinterpret_cast<float*>(ctx->ws + L.cs_off);
     uint16_t* q = reinterpret_cast<uint16_t*>(ctx->ws + L.q_off);
     uint16_t* a = reinterpret_cast<uint16_t*>(ctx->ws + L.a_off);
     float* o = reinterpret_cast<float*>(ctx->ws + L.o_off);
+    uint16_t *kc = layer_k(ctx, layer), *vc = layer_v(ctx, layer);
     const int d = c.d_model;
-    moe_status st;
     const int sq = moe_gemm_plain_split(T, L.nqkv), so = moe_gemm_plain_split(T, d);
-    const float* gamma = reinterpret_cast<const float*>(w);
     hipError_t e = timed(ctx, ATTN_K_NORM, s, [&] {
-        return attn_launch_norm(x, gamma, T, d, c.norm_eps, h, s);
+        return attn_launch_norm(x, reinterpret_cast<const float*>(w), T, d, c.norm_eps, h,
+                                reinterpret_cast<const double*>(w + L.freq_off), cs, c.head_dim, pos0, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "norm kernel launch");
-    e = timed(ctx, ATTN_K_QKV, s, [&] { return project(w + L.wqkv_off, h, d, L.nqkv, qkvp, T, sq, s); });
+    moe::GemmArgs g = product(w + L.wqkv_off, h, d, L.nqkv, sq > 1 ? part : qkv, T, sq);
+    g.cos_sin = cs;
+    g.q = q;
+    g.kc = kc;
+    g.vc = vc;
+    g.heads = c.n_heads;
+    g.kv_heads = c.n_kv_heads;
+    g.hd = c.head_dim;
+    g.max_seq = c.max_seq;
+    g.pos0 = pos0;
+    e = timed(ctx, ATTN_K_QKV, s, [&] { return sq > 1 ? moe_launch_gemm_down(&g, s) : moe_launch_gemm_qkv(&g, s); });
     if (e != hipSuccess) return hip_fail(ctx, e, "projection GEMM launch");
-    e = timed(ctx, ATTN_K_ROPE, s, [&] {
-        return attn_launch_rope(qkvp, reinterpret_cast<const double*>(w + L.freq_off), qkv, q,
-                                layer_k(ctx, layer), layer_v(ctx, layer), T, c.n_heads,
-                                c.n_kv_heads, c.head_dim, c.max_seq, pos0, sq, s);
-    });
-    if (e != hipSuccess) return hip_fail(ctx, e, "rotation kernel launch");
-    st = attention(ctx, layer, q, a, T, pos0, 0, s);
+    if (sq > 1) {
+        e = timed(ctx, ATTN_K_ROPE, s, [&] {
+            return attn_launch_rope(part, cs, qkv, q, kc, vc, T, c.n_heads, c.n_kv_heads, c.head_dim,
+                                    c.max_seq, pos0, sq, s);
+        });
+        if (e != hipSuccess) return hip_fail(ctx, e, "rotation kernel launch");
+    }
+    const moe_status st = attention(ctx, layer, q, a, T, pos0, 0, s);
     if (st != MOE_OK) return st;
-    e = timed(ctx, ATTN_K_OUT, s, [&] { return project(w + L.wo_off, a, L.nq, d, so > 1 ? qkvp : o, T, so, s); });
+    g = product(w + L.wo_off, a, L.nq, d, so > 1 ? part : o, T, so);
+    g.res = x;
+    g.y16 = y;
+    e = timed(ctx, ATTN_K_OUT, s, [&] { return so > 1 ? moe_launch_gemm_down(&g, s) : moe_launch_gemm_out(&g, s); });
     if (e != hipSuccess) return hip_fail(ctx, e, "output projection GEMM launch");
-    e = timed(ctx, ATTN_K_RESIDUAL, s, [&] {
-        return attn_launch_residual(x, o, qkvp, so, y, (int64_t)T * d, s);
-    });
-    if (e != hipSuccess) return hip_fail(ctx, e, "residual kernel launch");
+    if (so > 1) {
+        e = timed(ctx, ATTN_K_RESIDUAL, s, [&] {
+            return attn_launch_residual(x, part, so, o, y, (int64_t)T * d, s);
+        });
+        if (e != hipSuccess) return hip_fail(ctx, e, "residual kernel launch");
+    }
     return MOE_OK;
 }
 
@@ -306,7 +325,7 @@ moe_status forward_impl(attn_ctx* ctx, int32_t layer, const uint16_t* x, uint16_
     if (T > kDecodeTokens) return prefill(ctx, layer, x, y, T, pos0, s);
     if (!attn_norm_in_projection(T)) {
         e = timed(ctx, ATTN_K_NORM, s, [&] {
-            return attn_launch_norm(x, gamma, T, d, c.norm_eps, h, s);
+            return attn_launch_norm(x, gamma, T, d, c.norm_eps, h, nullptr, nullptr, 0, 0, s);
         });
         if (e != hipSuccess) return hip_fail(ctx, e, "norm kernel launch");
     }
@@ -470,7 +489,7 @@ moe_status attn_forward_norm(attn_ctx* ctx, int32_t layer, const uint16_t* x, ui
     if (st != MOE_OK) return st;
     const float* gamma2 = reinterpret_cast<const float*>(layer_w(ctx, layer) + ctx->L.gamma2_off);
     const hipError_t e = timed(ctx, ATTN_K_POST_NORM, s, [&] {
-        return attn_launch_norm(y, gamma2, T, ctx->cfg.d_model, ctx->cfg.norm_eps, z, s);
+        return attn_launch_norm(y, gamma2, T, ctx->cfg.d_model, ctx->cfg.norm_eps, z, nullptr, nullptr, 0, 0, s);
     });
     if (e != hipSuccess) return hip_fail(ctx, e, "post-attention norm launch");
     return MOE_OK;

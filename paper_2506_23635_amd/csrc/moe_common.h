@@ -136,6 +136,12 @@ struct GemmArgs {
     int mid;                  // take the 128 x 128 tiles, where
     int k_split;              // ... the reduction of a kDown is cut in k_split ranges, ...
     uint64_t split_stride;    // ... range i's sums at O + i * split_stride
+    // the attention block's products (O: their fp32 values)
+    const float* cos_sin;     // q|k|v: [T][hd/2][2], the tokens' rotations
+    uint16_t *q, *kc, *vc;    // q|k|v: rotated q [T][heads][hd]; the layer's caches
+    int heads, kv_heads, hd, max_seq, pos0;
+    const uint16_t* res;      // output: x [T, d], and y = bf16(x + o)
+    uint16_t* y16;
     uint64_t* stamps;         // per-workgroup timeline [max_stamps][8], or NULL (measurement)
     int max_stamps;
 };
@@ -166,6 +172,8 @@ hipError_t moe_launch_decode_gateup(const moe::DecodeArgs* a, int n_slots, hipSt
 hipError_t moe_launch_decode_down(const moe::DecodeArgs* a, int n_slots, hipStream_t s);
 hipError_t moe_launch_gemm_gateup(const moe::GemmArgs* a, hipStream_t s);
 hipError_t moe_launch_gemm_down(const moe::GemmArgs* a, hipStream_t s);
+hipError_t moe_launch_gemm_qkv(const moe::GemmArgs* a, hipStream_t s);
+hipError_t moe_launch_gemm_out(const moe::GemmArgs* a, hipStream_t s);
 int moe_prefill_tile_rows();
 int moe_gemm_mid_tiles(int T, int k, int E, int n_local, int M);
 int moe_gemm_plain_split(int T, int M);
@@ -177,7 +185,8 @@ hipError_t moe_launch_combine(const float* O, const int32_t* pair_row, const flo
 // Launchers of the attention-block kernels (attn.hip).
 extern "C" {
 hipError_t attn_launch_norm(const uint16_t* x, const float* gamma, int T, int d, float eps,
-                            uint16_t* h, hipStream_t s);
+                            uint16_t* h, const double* inv_freq, float* cos_sin, int hd, int pos0,
+                            hipStream_t s);
 int attn_norm_in_projection(int T);
 hipError_t attn_launch_qkv(const void* w, uint16_t* h, const uint16_t* x, const float* gamma,
                            float eps, const double* inv_freq, float* qkv, uint16_t* q,
@@ -185,7 +194,7 @@ hipError_t attn_launch_qkv(const void* w, uint16_t* h, const uint16_t* x, const 
                            int max_seq, int pos0, hipStream_t s);
 hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N, float* y32,
                            const uint16_t* res, uint16_t* y16, hipStream_t s);
-hipError_t attn_launch_rope(const float* qkvp, const double* inv_freq, float* qkv, uint16_t* q,
+hipError_t attn_launch_rope(const float* qkvp, const float* cos_sin, float* qkv, uint16_t* q,
                             uint16_t* kc, uint16_t* vc, int T, int H, int G, int hd, int max_seq,
                             int pos0, int n_split, hipStream_t s);
 int attn_part_stride(int hd);
@@ -201,6 +210,6 @@ hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16
                              int few, int n_split, hipStream_t s);
 hipError_t attn_launch_merge(const float* part, uint16_t* out, int T, int H, int hd, int n_split,
                              hipStream_t s);
-hipError_t attn_launch_residual(const uint16_t* x, float* o, const float* op, int n_split, uint16_t* y, int64_t n,
-                                hipStream_t s);
+hipError_t attn_launch_residual(const uint16_t* x, const float* op, int n_split, float* o, uint16_t* y,
+                                int64_t n, hipStream_t s);
 }

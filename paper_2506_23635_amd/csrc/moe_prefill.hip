@@ -69,7 +69,9 @@ __device__ inline f32x16_t mfma32x32x16(const u32x4_t a, const u32x4_t b, f32x16
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-enum { kGateUp = 0, kDown = 1 };
+// What a tile's sums become: kGateUp H, kDown O; the plain products of the
+// attention block are kDown with their own ends (kQkv, kOut).
+enum { kGateUp = 0, kDown = 1, kQkv = 2, kOut = 3 };
 
 // chunk swizzle of B row R in LDS (a function of R mod 16 only, so 32-row
 // token blocks share it): rows 0..7 take eight distinct slots, and rows
@@ -260,6 +262,162 @@ __device__ __forceinline__ void tile_loop(const TileCtx& c, int n_pairs, uint8_t
     __builtin_amdgcn_s_barrier();
 }
 
+// barrier for LDS traffic only: this wave's LDS operations are done, its
+// global stores may still be on their way
+__device__ __forceinline__ void lds_barrier()
+{
+    constexpr int kWaitLgkm = 0xC07F;   // lgkmcnt 0; vmcnt and expcnt at their maxima
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The end of a tile: kBlocks 32-feature blocks per wave (four waves, wave w
+// from row tile rt0 + 2 kBlocks w on) of up to kTBs 32-token blocks, token
+// rows row_start .. row_end - 1.  In a block the lane holds token lane % 32
+// and features 8g + 4 (lane / 32) + r in register 4g + r (g, r = 0..3).
+//
+// The sums go through LDS (free after the K loop), so that the workgroup
+// writes whole token rows: straight from the registers a store covers 16 or
+// 32 bytes of each of 32 rows, and with one workgroup per CU nothing hides
+// it (q|k|v of 2048 tokens, rotated here: 197 us from the registers).
+//  kGateUp  the block is 16 gate rows (g = 0, 1) and the 16 up rows of the
+//           same features (g = 2, 3): H = bf16(silu(G) U), all rows at once
+//  kDown    O (fp32), at the K range's offset; here and below 32 token rows
+//           at a time, through two buffers in turn
+//  kQkv     a row tile of a query or key head holds 8 rotation pairs, the
+//           first members in rows 0..7 and the second in rows 8..15 (the
+//           packing of rope_row): the fp32 values in natural order, rotated
+//           with the token's cos and sin, bf16 q to the workspace, k and v to
+//           the cache.  (A kernel of its own read and wrote the product once
+//           more: 45 us at 2048 tokens.)  Value rows keep their order, so
+//           their "pairs" are 8 features apart and stay unrotated.
+//  kOut     o (fp32) and y = bf16(x + o) (x and y may be the same array)
+template <int kMode, int kBlocks, int kTBs>
+__device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x16_t (&acc)[kBlocks][kTBs],
+                                           uint8_t* lds, int rt0, int row_start, int row_end, int w,
+                                           int lane, int split)
+{
+    constexpr int kFeat = 4 * kBlocks * 32;   // features of the workgroup
+    const int half = lane >> 5, c = lane & 31, tid = w * 64 + lane;
+    const int rows = row_end - row_start;
+    if constexpr (kMode == kGateUp) {
+        constexpr int kRow = kFeat + 16;      // bytes of a token's H features in LDS, padded
+        constexpr int kPieces = kFeat / 16;   // 16-byte pieces of them
+#pragma unroll
+        for (int t = 0; t < kTBs; ++t) {
+            if (t * 32 >= rows) break;
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) {
+                const f32x16_t v = acc[b][t];
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const uint32_t h01 = cvt_pk_bf16(silu_mul(v[4 * g + 0], v[4 * g + 8]),
+                                                     silu_mul(v[4 * g + 1], v[4 * g + 9]));
+                    const uint32_t h23 = cvt_pk_bf16(silu_mul(v[4 * g + 2], v[4 * g + 10]),
+                                                     silu_mul(v[4 * g + 3], v[4 * g + 11]));
+                    *reinterpret_cast<uint2*>(
+                        &lds[(t * 32 + c) * kRow + ((w * kBlocks + b) * 16 + 8 * g + 4 * half) * 2]) =
+                        make_uint2(h01, h23);
+                }
+            }
+        }
+        lds_barrier();
+#pragma unroll 4
+        for (int e = tid; e < rows * kPieces; e += kThreads) {
+            const int r = e / kPieces, p = e % kPieces;
+            *reinterpret_cast<u32x4_t*>(a.H + (int64_t)(row_start + r) * a.f + rt0 * 8 + p * 8) =
+                *reinterpret_cast<const u32x4_t*>(&lds[r * kRow + p * 16]);
+        }
+    } else {
+        constexpr int kRow = kFeat * 4 + 16;  // bytes of a token's sums in LDS, padded
+        // pieces of a token's row: 8 packed features (4 + 4 of a row tile) or
+        // 4; kIters of the 32 rows' pieces per thread
+        constexpr int kPieces = kFeat / (kMode == kQkv ? 8 : 4);
+        constexpr int kIters = 32 * kPieces / kThreads;
+        const int p = tid % kPieces, r0 = tid / kPieces;   // piece, first row
+        constexpr int kStep = kThreads / kPieces;          // rows between a thread's pieces
+        const int n0 = (rt0 + p / 2) * kTileRows, head = kMode == kQkv ? n0 / a.hd : 0;
+        const int hd = a.hd, e0 = kMode == kQkv ? n0 % hd : 0;
+        const bool turn = kMode == kQkv && head < a.heads + a.kv_heads;
+        const int f0 = (turn ? e0 / 2 : e0) + p % 2 * 4, gap = turn ? hd / 2 : 8;
+        // what the pieces need from memory, loaded a pass ahead: the tokens'
+        // cos and sin, or x (rows past the end: the last row's)
+        float4 cs[2][kMode == kQkv ? kIters : 1][2];
+        uint2 xr[2][kMode == kOut ? kIters : 1];
+        auto fetch = [&](int t) {
+#pragma unroll
+            for (int i = 0; i < kIters; ++i) {
+                const int64_t row = min(row_start + t * 32 + r0 + i * kStep, row_end - 1);
+                if constexpr (kMode == kQkv) {
+                    const float* src = a.cos_sin + (row * (hd / 2) + (turn ? f0 : 0)) * 2;
+                    cs[t % 2][i][0] = *reinterpret_cast<const float4*>(src);
+                    cs[t % 2][i][1] = *reinterpret_cast<const float4*>(src + 4);
+                }
+                if constexpr (kMode == kOut)
+                    xr[t % 2][i] = *reinterpret_cast<const uint2*>(a.res + row * a.d + rt0 * kTileRows + p * 4);
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int t = 0; t < kTBs; ++t) {
+            if (t * 32 >= rows) break;
+            uint8_t* buf = lds + t % 2 * (32 * kRow);
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<float4*>(&buf[c * kRow + ((w * kBlocks + b) * 32 + 8 * g + 4 * half) * 4]) =
+                        make_float4(acc[b][t][4 * g], acc[b][t][4 * g + 1], acc[b][t][4 * g + 2],
+                                    acc[b][t][4 * g + 3]);
+            lds_barrier();
+            if (t + 1 < kTBs) fetch(t + 1);
+#pragma unroll
+            for (int i = 0; i < kIters; ++i) {
+                const int r = r0 + i * kStep, row = row_start + t * 32 + r;
+                if (row >= row_end) continue;
+                if constexpr (kMode == kQkv) {
+                    const uint8_t* src = &buf[r * kRow + (p / 2 * 16 + p % 2 * 4) * 4];
+                    const float4 x0 = *reinterpret_cast<const float4*>(src);
+                    const float4 x1 = *reinterpret_cast<const float4*>(src + 32);
+                    const float4 c01 = cs[t % 2][i][0], c23 = cs[t % 2][i][1];
+                    float4 y0 = x0, y1 = x1;
+                    if (turn) {
+                        y0 = make_float4(x0.x * c01.x - x1.x * c01.y, x0.y * c01.z - x1.y * c01.w,
+                                         x0.z * c23.x - x1.z * c23.y, x0.w * c23.z - x1.w * c23.w);
+                        y1 = make_float4(x1.x * c01.x + x0.x * c01.y, x1.y * c01.z + x0.y * c01.w,
+                                         x1.z * c23.x + x0.z * c23.y, x1.w * c23.z + x0.w * c23.w);
+                    }
+                    float* nat = a.O + (int64_t)row * a.d + head * hd + f0;
+                    *reinterpret_cast<float4*>(nat) = x0;
+                    *reinterpret_cast<float4*>(nat + gap) = x1;
+                    uint16_t* dst =
+                        head < a.heads ? a.q + ((int64_t)row * a.heads + head) * hd
+                        : turn ? a.kc + ((int64_t)(head - a.heads) * a.max_seq + a.pos0 + row) * hd
+                               : a.vc + ((int64_t)(head - a.heads - a.kv_heads) * a.max_seq + a.pos0 + row) * hd;
+                    *reinterpret_cast<uint2*>(dst + f0) =
+                        make_uint2(cvt_pk_bf16(y0.x, y0.y), cvt_pk_bf16(y0.z, y0.w));
+                    *reinterpret_cast<uint2*>(dst + f0 + gap) =
+                        make_uint2(cvt_pk_bf16(y1.x, y1.y), cvt_pk_bf16(y1.z, y1.w));
+                } else {
+                    const int64_t at = (int64_t)row * a.d + rt0 * kTileRows + p * 4;
+                    const float4 v = *reinterpret_cast<const float4*>(&buf[r * kRow + p * 16]);
+                    *reinterpret_cast<float4*>(a.O + (uint64_t)split * a.split_stride + at) = v;
+                    if constexpr (kMode == kOut) {
+                        const uint2 x = xr[t % 2][i];
+                        *reinterpret_cast<uint2*>(a.y16 + at) =
+                            make_uint2(cvt_pk_bf16(__uint_as_float(x.x << 16) + v.x,
+                                                   __uint_as_float(x.x & 0xFFFF0000u) + v.y),
+                                       cvt_pk_bf16(__uint_as_float(x.y << 16) + v.z,
+                                                   __uint_as_float(x.y & 0xFFFF0000u) + v.w));
+                    }
+                }
+            }
+        }
+    }
+}
+
 // One BM x BN tile (feature tile ft, token tile tt) of the grouped GEMM.
 template <int kMode>
 __device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_start, int row_end, int ft, uint8_t* lds)
@@ -337,40 +495,7 @@ __device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_s
     else
         tile_loop<false>(c, (ntb + 1) / 2, lds, acc);
 
-    // epilogue: in a 32 x 32 block lane l holds token column l%32 and rows
-    // 8g + 4(l/32) + r in register 4g + r (g, r = 0..3).  A 32-row block is
-    // row tiles (rt, rt + 1): for the gate/up GEMM that is 16 gate rows
-    // (g = 0, 1) and the 16 up rows of the same features (g = 2, 3).
-    const int half = lane >> 5;
-    const int jcol = lane & 31;
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        const int row = row_start + tb * 32 + jcol;
-        if (row >= row_end) continue;
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb) {
-            const f32x16_t v = acc[fb][tb];
-            const uint64_t rt = rt0 + 2 * fb;
-            if (kMode == kGateUp) {
-#pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    const int feat = (int)(rt / 2) * 16 + 8 * g + 4 * half;
-                    const uint32_t h01 = cvt_pk_bf16(silu_mul(v[4 * g + 0], v[4 * g + 8]),
-                                                     silu_mul(v[4 * g + 1], v[4 * g + 9]));
-                    const uint32_t h23 = cvt_pk_bf16(silu_mul(v[4 * g + 2], v[4 * g + 10]),
-                                                     silu_mul(v[4 * g + 3], v[4 * g + 11]));
-                    *reinterpret_cast<uint2*>(a.H + (int64_t)row * a.f + feat) = make_uint2(h01, h23);
-                }
-            } else {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int feat = (int)rt * 16 + 8 * g + 4 * half;
-                    *reinterpret_cast<float4*>(a.O + (int64_t)row * a.d + feat) =
-                        make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
-                }
-            }
-        }
-    }
+    store_tile<kMode, FB, TB>(a, acc, lds, ft * (BM / 16), row_start, row_end, w, lane, 0);
 }
 
 // Measurement only (a.stamps, set by moe_profile_gemm_timeline): workgroup
@@ -657,41 +782,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_mid_kernel(GemmArgs a)
         const int R = lane & 31;
         c.rd_off[j] = (uint32_t)R * (BK * 2) + (uint32_t)(((2 * j + (lane >> 5)) ^ b_swizzle(R)) * 16);
     }
-    f32x16_t acc[kMidTB];
+    f32x16_t acc[1][kMidTB];
 #pragma unroll
-    for (int t = 0; t < kMidTB; ++t) acc[t] = f32x16_t{};
+    for (int t = 0; t < kMidTB; ++t) acc[0][t] = f32x16_t{};
     if (tp.n_sub == 1)
-        mid_loop_any<true>(tb, c, lds, acc);
+        mid_loop_any<true>(tb, c, lds, acc[0]);
     else
-        mid_loop_any<false>(tb, c, lds, acc);
+        mid_loop_any<false>(tb, c, lds, acc[0]);
 
-    // epilogue as gemm_kernel's
-    const int half = lane >> 5;
-#pragma unroll
-    for (int t = 0; t < kMidTB; ++t) {
-        const int row = row_start + t * 32 + (lane & 31);
-        if (t >= tb || row >= row_end) continue;
-        const f32x16_t v = acc[t];
-        if (kMode == kGateUp) {
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const int feat = (int)(rt / 2) * 16 + 8 * g + 4 * half;
-                const uint32_t h01 = cvt_pk_bf16(silu_mul(v[4 * g + 0], v[4 * g + 8]),
-                                                 silu_mul(v[4 * g + 1], v[4 * g + 9]));
-                const uint32_t h23 = cvt_pk_bf16(silu_mul(v[4 * g + 2], v[4 * g + 10]),
-                                                 silu_mul(v[4 * g + 3], v[4 * g + 11]));
-                *reinterpret_cast<uint2*>(a.H + (int64_t)row * a.f + feat) = make_uint2(h01, h23);
-            }
-        } else {
-            float* out = a.O + (uint64_t)split * a.split_stride + (int64_t)row * a.d;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int feat = (int)rt * 16 + 8 * g + 4 * half;
-                *reinterpret_cast<float4*>(out + feat) =
-                    make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
-            }
-        }
-    }
+    store_tile<kMode, 1, kMidTB>(a, acc, lds, ft * (MBM / 16), row_start, row_end, w, lane, split);
 }
 
 }  // namespace moe
@@ -703,19 +802,21 @@ int moe_prefill_tile_rows() { return moe::BN; }
 // Whether a grouped GEMM of M features per expert takes the 128 x 128 tiles:
 // T tokens, k of E experts each, n_local experts here (a plain product: k =
 // E = n_local = 1).
-//  - Up to about 112 rows per expert the weight stream bounds it (d 6144, f
-//    10752, all 16 experts, whole layer, 256 x 256 tiles -> 128 x 128: 17
-//    tokens 1129 -> 965 us, 128 tokens 1220 -> 1048, 400 tokens (100 rows)
-//    1288 -> 1214; 500 tokens (125 rows) 1338 -> 1496).
+//  - Up to about 96 rows per expert the weight stream bounds it (d 6144, f
+//    10752, all 16 experts, whole layer, 256 x 256 tiles -> 128 x 128, and
+//    with skewed loads: 17 tokens 1131 -> 965 us; 200 tokens (50 rows) 1177 ->
+//    1053, skewed 1237 -> 1132; 350 (88 rows) 1278 -> 1204, skewed 1309 ->
+//    1311; 400 (100 rows) 1287 -> 1244, skewed 1341 -> 1357; 480 (120 rows)
+//    1328 -> 1437, skewed 1383 -> 1538).
 //  - With at most 128 tiles of 256 x 256 half of the CUs or more would have
 //    none (d 6144: 600 tokens through the 8192-wide projection, 96 tiles,
-//    and the 6144-wide one, 72 tiles, the attention block 272 -> 216 us; 1024
-//    tokens, 128 and 96 tiles, 318 -> 304; 1400 tokens, 192 and 144 tiles,
-//    355 -> 411).
+//    and the 6144-wide one, 72 tiles, the attention block 253 -> 199 us; 1024
+//    tokens, 128 and 96 tiles, 299 -> 286; 1400 tokens, 192 and 144 tiles,
+//    324 -> 386).
 int moe_gemm_mid_tiles(int T, int k, int E, int n_local, int M)
 {
     const int64_t pairs = (int64_t)T * k;
-    if (pairs <= (int64_t)112 * E) return 1;
+    if (pairs <= (int64_t)96 * E) return 1;
     const int64_t rows = (pairs + E - 1) / E;
     return (int64_t)(M / moe::BM) * n_local * ((rows + moe::BN - 1) / moe::BN) <= 128;
 }
@@ -760,13 +861,28 @@ static hipError_t launch_gemm_mid(const moe::GemmArgs* a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int kMode>
+static hipError_t launch_any(const moe::GemmArgs* a, hipStream_t s)
+{
+    return a->mid ? launch_gemm_mid<kMode>(a, s) : launch_gemm<kMode>(a, s);
+}
+
 extern "C" hipError_t moe_launch_gemm_gateup(const moe::GemmArgs* a, hipStream_t s)
 {
-    return a->mid ? launch_gemm_mid<moe::kGateUp>(a, s) : launch_gemm<moe::kGateUp>(a, s);
+    return launch_any<moe::kGateUp>(a, s);
 }
 
 extern "C" hipError_t moe_launch_gemm_down(const moe::GemmArgs* a, hipStream_t s)
 {
-    return a->mid ? launch_gemm_mid<moe::kDown>(a, s) : launch_gemm<moe::kDown>(a, s);
+    return launch_any<moe::kDown>(a, s);
 }
 
+extern "C" hipError_t moe_launch_gemm_qkv(const moe::GemmArgs* a, hipStream_t s)
+{
+    return launch_any<moe::kQkv>(a, s);
+}
+
+extern "C" hipError_t moe_launch_gemm_out(const moe::GemmArgs* a, hipStream_t s)
+{
+    return launch_any<moe::kOut>(a, s);
+}
