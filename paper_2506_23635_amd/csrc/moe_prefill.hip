@@ -57,6 +57,7 @@ constexpr int B_LOADS = B_FRAGS * 64 / kThreads;  // 8 per thread
 constexpr int B_STAGE_BYTES = B_FRAGS * kTileBytes;  // 32 KiB
 constexpr int kXcds = 8;
 constexpr int kBufferFlags = 0x00020000;   // buffer descriptor word 3 (raw dword data, gfx9 family)
+constexpr int kNonTemporal = 2;              // buffer cache policy
 constexpr int kWaitAll = (0x7 << 4) | (0xF << 8);   // vmcnt 0
 static_assert(kRingA == 3, "the K loop is unrolled by three stages");
 static_assert(kRingB == 4, "stage s reads B(s), publishes B(s+1), loads B(s+2)");
@@ -262,6 +263,105 @@ __device__ __forceinline__ void tile_loop(const TileCtx& c, int n_pairs, uint8_t
     __builtin_amdgcn_s_barrier();
 }
 
+// A tile of at most 128 token rows (kTB 32-token blocks; an expert's only
+// or last tile).  With half of the accumulators free the wave keeps kRingH
+// stages of A in flight instead of three: a tile with few rows is bound by
+// the latency of its weight stream, not by its MFMAs (three stages: a 64-row
+// tile took 121 us of a full one's 155; whole layer at 500 tokens, d 6144, f
+// 10752: 1332 -> 1263 us, 400: 1241 -> 1174; no change from 700 tokens on).  B fragments are read one K step
+// ahead, across stages too: before the last K step the wave waits for its
+// own reads of the stage's buffer and for its part of B(s+1), then a barrier
+// publishes both.  At its start stage s issues B(s+3) into the buffer that
+// stage s-1 read; A(s + kRingH) refills each fragment after its last use, in
+// every stage (past the end it re-reads the last stage), so that the counts
+// hold throughout: after B(s+1), issued at the start of stage s-2, came that
+// stage's A refills, the B loads and A refills of stage s-1, and the B loads
+// and the first three K steps' refills of stage s.
+constexpr int kRingH = 6;
+constexpr int kHalfTB = TB / 2;
+
+template <int kTB, bool kOnce>
+__device__ __forceinline__ void half_loop(const TileCtx& c, uint8_t* lds, f32x16_t (&acc)[FB][kHalfTB])
+{
+    constexpr int kStage = kTB * 32 * BK * 2;
+    constexpr int kWait = wait_vm(2 * kTB + 3 * A_FRAGS - FB);
+    static_assert(2 * kTB + 3 * A_FRAGS - FB < 64, "vmcnt holds 6 bits");
+    const int n_stages = c.n_stages, w = c.w;
+    u32x4_t ra[kRingH][A_FRAGS];
+    auto load_a1 = [&](int s, int fb, int j, u32x4_t& dst) {
+        dst = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                              c.a_rsrc, c.a_off[fb] + (j / 2) * kTileBytes + (j % 2) * (kTileBytes / 2),
+                                              (uint32_t)s * (2 * kTileBytes), kOnce ? kNonTemporal : 0));
+    };
+    // load q of wave w: rows 32 q + 8 w .. + 7, whole 128-byte lines
+    auto load_b = [&](int s, int buf) {
+#pragma unroll
+        for (int q = 0; q < kTB; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                c.b_rsrc, (__attribute__((address_space(3))) void*)(&lds[buf + (q * 4 + w) * kTileBytes]),
+                16, c.b_off[q], (uint32_t)s * (BK * 2), 0, 0);
+    };
+    u32x4_t bw[2][kTB];                        // B fragments of two K steps in turn
+    auto read_b = [&](int buf, int j, u32x4_t (&dst)[kTB]) {
+#pragma unroll
+        for (int t = 0; t < kTB; ++t)
+            dst[t] = *reinterpret_cast<const u32x4_t*>(&lds[buf + c.rd_off[j] + t * 32 * (BK * 2)]);
+    };
+    int cur = 0, prev = (kRingB - 1) * kStage;   // byte offsets of this and the last stage's buffer
+    auto stage = [&](int s, u32x4_t (&A)[A_FRAGS]) {
+        const int next = cur + kStage == kRingB * kStage ? 0 : cur + kStage;
+        const int sa = min(s + kRingH, n_stages - 1);
+        load_b(min(s + kRingB - 1, n_stages - 1), prev);
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+            if (j + 1 == KS) {
+                __builtin_amdgcn_s_waitcnt(kWait & ~(0xF << 8));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                read_b(next, 0, bw[0]);
+            } else {
+                read_b(cur, j + 1, bw[(j + 1) & 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < kTB; ++t)
+#pragma unroll
+                for (int fb = 0; fb < FB; ++fb)
+                    acc[fb][t] = mfma32x32x16(A[fb * KS + j], bw[j & 1][t], acc[fb][t]);
+#pragma unroll
+            for (int fb = 0; fb < FB; ++fb) load_a1(sa, fb, j, A[fb * KS + j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        prev = cur;
+        cur = next;
+    };
+#pragma unroll
+    for (int i = 0; i < kRingH; ++i)
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+            for (int j = 0; j < KS; ++j) load_a1(min(i, n_stages - 1), fb, j, ra[i][fb * KS + j]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i + 1 < kRingB; ++i) load_b(min(i, n_stages - 1), i * kStage);
+    __builtin_amdgcn_s_waitcnt(kWaitAll);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read_b(0, 0, bw[0]);
+    for (int s = 0; s < n_stages; s += kRingH) {
+        stage(s, ra[0]);
+        if (s + 1 < n_stages) stage(s + 1, ra[1]);
+        if (s + 2 < n_stages) stage(s + 2, ra[2]);
+        if (s + 3 < n_stages) stage(s + 3, ra[3]);
+        if (s + 4 < n_stages) stage(s + 4, ra[4]);
+        if (s + 5 < n_stages) stage(s + 5, ra[5]);
+    }
+    // drain the dummy loads before the epilogue takes the LDS
+    __builtin_amdgcn_s_waitcnt(kWaitAll);
+    __builtin_amdgcn_s_barrier();
+}
+
 // barrier for LDS traffic only: this wave's LDS operations are done, its
 // global stores may still be on their way
 __device__ __forceinline__ void lds_barrier()
@@ -420,9 +520,10 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x16_t (&a
 
 // One BM x BN tile (feature tile ft, token tile tt) of the grouped GEMM.
 template <int kMode>
-__device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_start, int row_end, int ft, uint8_t* lds)
+__device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_start, int row_end, bool once, int ft, uint8_t* lds)
 {
     const int ntb = (row_end - row_start + 31) / 32;   // 32-token blocks with rows
+    const bool half = ntb <= kHalfTB;                  // half_loop's tile
 
     const int K = kMode == kGateUp ? a.d : a.f;
     const uint64_t KT = (uint64_t)K / kTileK;
@@ -452,7 +553,8 @@ __device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_s
     // 128 bytes of K [64 s, 64 s + 64) as eight 16-byte chunks; chunk c sits
     // in slot c ^ swz(R) so that the MFMA reads (8 consecutive rows at one
     // chunk) fall in distinct LDS banks.  Load q of wave w: lane l reads row
-    // R = 64w + 8q + l/8, slot l%8, i.e. chunk (l%8) ^ swz(R).  Gate/up
+    // R = 64w + 8q + l/8 (a tile of at most
+    // 128 rows: R = 32q + 8w + l/8), slot l%8, i.e. chunk (l%8) ^ swz(R).  Gate/up
     // gathers rows of x (the library caps T*d*2 below 2^31, so byte offsets
     // fit 32 bits); down reads the tile's own rows of H through a buffer
     // based at the tile's first row.  The buffer size bounds every load
@@ -465,7 +567,7 @@ __device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_s
                                                      (row_end - row_start) * a.f * 2, kBufferFlags);
 #pragma unroll
     for (int q = 0; q < B_LOADS; ++q) {
-        const int R = w * 64 + q * 8 + (lane >> 3);
+        const int R = half ? q % 4 * 32 + w * 8 + (lane >> 3) : w * 64 + q * 8 + (lane >> 3);
         const int row = row_start + R;
         const int rr = row < row_end ? row : row_start;   // rows past the end: any valid row
         const uint32_t chunk = (uint32_t)((lane & 7) ^ b_swizzle(R)) * 16;
@@ -482,6 +584,19 @@ __device__ __forceinline__ void process_tile(const GemmArgs& a, int e, int row_s
         c.rd_off[j] = (uint32_t)R * (BK * 2) + (uint32_t)(((2 * j + (lane >> 5)) ^ b_swizzle(R)) * 16);
     }
 
+    if (half) {
+        f32x16_t acc[FB][kHalfTB];
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+            for (int tb = 0; tb < kHalfTB; ++tb) acc[fb][tb] = f32x16_t{};
+        if (ntb <= 2)
+            once ? half_loop<2, true>(c, lds, acc) : half_loop<2, false>(c, lds, acc);
+        else
+            once ? half_loop<4, true>(c, lds, acc) : half_loop<4, false>(c, lds, acc);
+        store_tile<kMode, FB, kHalfTB>(a, acc, lds, ft * (BM / 16), row_start, row_end, w, lane, 0);
+        return;
+    }
     f32x16_t acc[FB][TB];
 #pragma unroll
     for (int fb = 0; fb < FB; ++fb)
@@ -585,7 +700,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmArgs a)
         r0 = __builtin_amdgcn_s_memrealtime();
         c0 = __builtin_amdgcn_s_memtime();
     }
-    process_tile<kMode>(a, e, row_start, row_end, ft, lds);
+    process_tile<kMode>(a, e, row_start, row_end, tp.n_sub == 1, ft, lds);
     if (stamp) write_stamp(a, r0, c0, ft, tt, row_end - row_start, e);
 }
 
@@ -610,7 +725,6 @@ constexpr int MBN = 128;           // token rows per workgroup tile
 constexpr int kMidTB = MBN / 32;   // 32-token blocks at most
 constexpr int kMidRing = 4;        // A stages in registers
 constexpr int kMidRingB = 4;       // B stages in LDS
-constexpr int kNonTemporal = 2;    // buffer cache policy
 
 struct MidCtx {
     __amdgpu_buffer_rsrc_t a_rsrc, b_rsrc;
@@ -802,12 +916,12 @@ int moe_prefill_tile_rows() { return moe::BN; }
 // Whether a grouped GEMM of M features per expert takes the 128 x 128 tiles:
 // T tokens, k of E experts each, n_local experts here (a plain product: k =
 // E = n_local = 1).
-//  - Up to about 96 rows per expert the weight stream bounds it (d 6144, f
+//  - Up to about 64 rows per expert the weight stream bounds it (d 6144, f
 //    10752, all 16 experts, whole layer, 256 x 256 tiles -> 128 x 128, and
-//    with skewed loads: 17 tokens 1131 -> 965 us; 200 tokens (50 rows) 1177 ->
-//    1053, skewed 1237 -> 1132; 350 (88 rows) 1278 -> 1204, skewed 1309 ->
-//    1311; 400 (100 rows) 1287 -> 1244, skewed 1341 -> 1357; 480 (120 rows)
-//    1328 -> 1437, skewed 1383 -> 1538).
+//    with skewed loads: 17 tokens 1023 -> 970 us; 128 tokens (32 rows) 1123 ->
+//    1049, skewed 1125 -> 1071; 200 (50 rows) 1147 -> 1088, skewed 1153 ->
+//    1133; 260 (65 rows) 1170 -> 1139, skewed 1185 -> 1209; 350 (88 rows) 1213
+//    -> 1206, skewed 1239 -> 1313).
 //  - With at most 128 tiles of 256 x 256 half of the CUs or more would have
 //    none (d 6144: 600 tokens through the 8192-wide projection, 96 tiles,
 //    and the 6144-wide one, 72 tiles, the attention block 253 -> 199 us; 1024
@@ -816,7 +930,7 @@ int moe_prefill_tile_rows() { return moe::BN; }
 int moe_gemm_mid_tiles(int T, int k, int E, int n_local, int M)
 {
     const int64_t pairs = (int64_t)T * k;
-    if (pairs <= (int64_t)96 * E) return 1;
+    if (pairs <= (int64_t)64 * E) return 1;
     const int64_t rows = (pairs + E - 1) / E;
     return (int64_t)(M / moe::BM) * n_local * ((rows + moe::BN - 1) / moe::BN) <= 128;
 }
