@@ -45,7 +45,11 @@ using moe::kTileBytes;
 using moe::kTileRows;
 
 constexpr int kSplit = 8;          // waves per GEMV workgroup (K split)
-constexpr int kUnroll = 8;         // K tiles per wave in flight
+constexpr int kUnroll = 8;         // K tiles per wave and batch, tokens from LDS
+// K tiles per wave and batch, tokens from memory: their fragments are loaded
+// a batch ahead too, and with eight tiles both buffers would not leave two
+// workgroups per CU their registers
+constexpr int kUnrollX = 4;
 constexpr int kChunk = 64;         // positions per score_kernel workgroup
 constexpr int kPartPad = 4;        // m, l and padding after the hd sums of a partial
 
@@ -55,6 +59,58 @@ __device__ inline u32x4_t ld16_nt(const void* p)
 }
 
 __device__ inline u32x4_t ld16(const void* p) { return *reinterpret_cast<const u32x4_t*>(p); }
+
+// The full batches of a projection's reduction with the tokens in memory:
+// kUnrollX K tiles per wave and batch, weights and token fragments in two
+// buffers in turn, the next batch's loads issued before this batch's MFMAs,
+// so that both stay in flight while it is multiplied.  (With the token
+// fragments loaded in their own batch every batch waited one cache latency
+// for them: with this and the epilogues' loads and rotations ahead of the
+// stream, the DBRX block at one token after 2047 positions 43.7 -> 42.2 us, at
+// 16 tokens after 100 66.8 -> 64.8; three tiles per batch 41.9 and 64.0, but
+// 24.6 against 23.8 at d 2048; six 42.3 and 66.8.)  The loads have no branches (an unused column reads token
+// 0's row and feeds zeros), so a wait for them is not a wait for everything.
+// kt: K tiles done; `meanwhile` runs once while the first loads are in flight.
+template <class F>
+__device__ __forceinline__ void stream_batches(const uint8_t* pw, const uint16_t* px, int nb, int w,
+                                               bool has_tok, f32x4_t& acc, int& kt, F&& meanwhile)
+{
+    constexpr int kStep = kSplit * kUnrollX;
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
+    auto load = [&](int b, u32x4_t* wt, u32x4_t* xv) {
+#pragma unroll
+        for (int u = 0; u < kUnrollX; ++u) xv[u] = ld16(px + (b * kStep + w + kSplit * u) * kTileK);
+#pragma unroll
+        for (int u = 0; u < kUnrollX; ++u)
+            wt[u] = ld16_nt(pw + (int64_t)(b * kStep + w + kSplit * u) * kTileBytes);
+    };
+    auto mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
+#pragma unroll
+        for (int u = 0; u < kUnrollX; ++u) acc = moe::mfma16x16x32(wt[u], has_tok ? xv[u] : zero, acc);
+    };
+    if (nb == 0) {
+        meanwhile();
+        return;
+    }
+    u32x4_t wa[kUnrollX], wb[kUnrollX], xa[kUnrollX], xb[kUnrollX];
+    load(0, wa, xa);
+    meanwhile();
+    int b = 0;
+    for (; b + 2 < nb; b += 2) {
+        load(b + 1, wb, xb);
+        mfmas(wa, xa);
+        load(b + 2, wa, xa);
+        mfmas(wb, xb);
+    }
+    if (b + 1 < nb) {
+        load(b + 1, wb, xb);
+        mfmas(wa, xa);
+        mfmas(wb, xb);
+    } else {
+        mfmas(wa, xa);
+    }
+    kt = nb * kStep;
+}
 
 // The output projection, o = a Wo (fp32) and y = bf16(x + o), one
 // workgroup per 16 output features.
@@ -79,53 +135,12 @@ __global__ __launch_bounds__(64 * kSplit) void gemv_kernel(GemvArgs a)
     const uint16_t* px = a.x + (has_tok ? (int64_t)j * a.K : 0) + g * 8;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     const u32x4_t zero = {0u, 0u, 0u, 0u};
-    constexpr int kStep = kSplit * kUnroll;
-    const int nb = KT / kStep;                 // full batches of kUnroll tiles per wave
-    // token loads without branches (an unused column reads token 0's row and
-    // feeds zeros), so that a wait for them is not a wait for everything
-    auto xload = [&](int k0, u32x4_t* xv) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const u32x4_t v = ld16(px + (k0 + w + kSplit * u) * kTileK);
-            xv[u] = has_tok ? v : zero;
-        }
-    };
-    auto wload = [&](int k0, u32x4_t* wt) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            wt[u] = ld16_nt(pw + (int64_t)(k0 + w + kSplit * u) * kTileBytes);
-    };
-    auto mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) acc = moe::mfma16x16x32(wt[u], xv[u], acc);
-    };
+    // the residual of the lane's outputs, loaded ahead of the weights (output
+    // features 16q + 4g .. +3 of token j; other lanes read token 0's)
+    const int64_t o = (int64_t)(has_tok ? j : 0) * a.N + q * kTileRows + g * 4;
+    const uint2 r = *reinterpret_cast<const uint2*>(a.res + o);
     int kt = 0;
-    if (nb > 0) {
-        // two weight buffers in turn: the next batch's weights are issued
-        // after this batch's token loads and before its MFMAs, so they stay
-        // in flight while it is multiplied
-        u32x4_t wa[kUnroll], wb[kUnroll], xv[kUnroll];
-        wload(0, wa);
-        int b = 0;
-        for (; b + 2 < nb; b += 2) {
-            xload(b * kStep, xv);
-            wload((b + 1) * kStep, wb);
-            mfmas(wa, xv);
-            xload((b + 1) * kStep, xv);
-            wload((b + 2) * kStep, wa);
-            mfmas(wb, xv);
-        }
-        xload(b * kStep, xv);
-        if (b + 1 < nb) {
-            wload((b + 1) * kStep, wb);
-            mfmas(wa, xv);
-            xload((b + 1) * kStep, xv);
-            mfmas(wb, xv);
-        } else {
-            mfmas(wa, xv);
-        }
-        kt = nb * kStep;
-    }
+    stream_batches(pw, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, [] {});
     for (kt += w; kt < KT; kt += kSplit) {
         const u32x4_t wt = ld16_nt(pw + (int64_t)kt * kTileBytes);
         const u32x4_t xt = has_tok ? ld16(px + kt * kTileK) : zero;
@@ -136,10 +151,7 @@ __global__ __launch_bounds__(64 * kSplit) void gemv_kernel(GemvArgs a)
     if (w != 0) return;
     for (int i = 0; i + 1 < kSplit; ++i) acc += s_red[i * 64 + lane];
     if (!has_tok) return;
-    // lane holds output features 16q + 4g .. +3 of token j
-    const int64_t o = (int64_t)j * a.N + q * kTileRows + g * 4;
     *reinterpret_cast<float4*>(a.y32 + o) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    const uint2 r = *reinterpret_cast<const uint2*>(a.res + o);
     const float r0 = __uint_as_float(r.x << 16), r1 = __uint_as_float(r.x & 0xFFFF0000u);
     const float r2 = __uint_as_float(r.y << 16), r3 = __uint_as_float(r.y & 0xFFFF0000u);
     const uint32_t lo = (uint32_t)moe::f32_to_bf16(r0 + acc[0]) |
@@ -295,6 +307,21 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     const u32x4_t zero = {0u, 0u, 0u, 0u};
     u32x4_t wv[kUnroll], xb[kUnroll];
+    // the rotations that the epilogue applies, formed while the first weights
+    // are in flight (in the epilogue they were a chain of their own behind
+    // the stream): wave e < 4 forms those of the lanes' e-th pairs
+    __shared__ float2 s_cs[4][64];
+    const int row0 = q * kTileRows, nqk_rows = (a.H + a.G) * a.hd;
+    const bool turn = row0 < nqk_rows;
+    const int fr = 8 * ((row0 % a.hd) / kTileRows) + 4 * (g & 1) + (w & 3);   // frequency of wave w's pair
+    const double inv_fr = a.inv_freq[turn ? fr : 0];
+    auto rotations = [&] {
+        if (turn && w < 4) {
+            float c, sf;
+            rope_cs(a.pos0 + j, inv_fr, c, sf);
+            s_cs[w][lane] = make_float2(c, sf);
+        }
+    };
     if constexpr (kNorm) {
         __shared__ double red[2][kLnMaxT][kSplit];
         const int tid = threadIdx.x, ng = a.d / 8;
@@ -322,6 +349,7 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u)
             wv[u] = ld16_nt(pw + (int64_t)min(w + kSplit * u, KT - 1) * kTileBytes);
+        rotations();
 #pragma unroll
         for (int t = 0; t < kLnMaxT; ++t) {
             if (t >= a.T) break;
@@ -370,54 +398,52 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
         }
         lds_barrier();
     }
-    // two weight buffers in turn, as gemv_kernel (with kNorm the first batch
-    // was issued above, into wv)
-    constexpr int kStep = kSplit * kUnroll;
-    const int nb = KT / kStep;
     int kt = 0;
-    auto xload = [&](int k0, u32x4_t* xv) {
+    if constexpr (!kNorm) {
+        stream_batches(pw, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, rotations);
+    } else {
+        // two weight buffers in turn (the first batch was issued above, into
+        // wv), tokens from LDS
+        constexpr int kStep = kSplit * kUnroll;
+        const int nb = KT / kStep;
+        auto xload = [&](int k0, u32x4_t* xv) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int ko = (k0 + w + kSplit * u) * kTileK;
-            if constexpr (kNorm) {
+            for (int u = 0; u < kUnroll; ++u) {
+                const int ko = (k0 + w + kSplit * u) * kTileK;
                 xv[u] = has_tok ? *reinterpret_cast<const u32x4_t*>(hx + ko) : zero;
-            } else {
-                const u32x4_t v = ld16(px + ko);
-                xv[u] = has_tok ? v : zero;
             }
-        }
-    };
-    auto wload = [&](int k0, u32x4_t* wt) {
+        };
+        auto wload = [&](int k0, u32x4_t* wt) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            wt[u] = ld16_nt(pw + (int64_t)(k0 + w + kSplit * u) * kTileBytes);
-    };
-    auto mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
+            for (int u = 0; u < kUnroll; ++u)
+                wt[u] = ld16_nt(pw + (int64_t)(k0 + w + kSplit * u) * kTileBytes);
+        };
+        auto mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) acc = moe::mfma16x16x32(wt[u], xv[u], acc);
-    };
-    if (nb > 0) {
-        u32x4_t wb[kUnroll];
-        if constexpr (!kNorm) wload(0, wv);
-        int b = 0;
-        for (; b + 2 < nb; b += 2) {
+            for (int u = 0; u < kUnroll; ++u) acc = moe::mfma16x16x32(wt[u], xv[u], acc);
+        };
+        if (nb > 0) {
+            u32x4_t wb[kUnroll];
+            int b = 0;
+            for (; b + 2 < nb; b += 2) {
+                xload(b * kStep, xb);
+                wload((b + 1) * kStep, wb);
+                mfmas(wv, xb);
+                xload((b + 1) * kStep, xb);
+                wload((b + 2) * kStep, wv);
+                mfmas(wb, xb);
+            }
             xload(b * kStep, xb);
-            wload((b + 1) * kStep, wb);
-            mfmas(wv, xb);
-            xload((b + 1) * kStep, xb);
-            wload((b + 2) * kStep, wv);
-            mfmas(wb, xb);
+            if (b + 1 < nb) {
+                wload((b + 1) * kStep, wb);
+                mfmas(wv, xb);
+                xload((b + 1) * kStep, xb);
+                mfmas(wb, xb);
+            } else {
+                mfmas(wv, xb);
+            }
+            kt = nb * kStep;
         }
-        xload(b * kStep, xb);
-        if (b + 1 < nb) {
-            wload((b + 1) * kStep, wb);
-            mfmas(wv, xb);
-            xload((b + 1) * kStep, xb);
-            mfmas(wb, xb);
-        } else {
-            mfmas(wv, xb);
-        }
-        kt = nb * kStep;
     }
     for (kt += w; kt < KT; kt += kSplit) {
         const u32x4_t wt = ld16_nt(pw + (int64_t)kt * kTileBytes);
@@ -435,7 +461,6 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
     if (!has_tok) return;
     const int hd = a.hd, half = hd / 2;
     const int nqk = (a.H + a.G) * hd, nqkv = nqk + a.G * hd;
-    const int row0 = q * kTileRows;
     const int pos = a.pos0 + j;
     float* qrow = a.qkv + (int64_t)j * nqkv;
     uint16_t* dst;
@@ -449,9 +474,8 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float partner = __shfl_xor(acc[e], 32, 64);
-            float c, sf;
-            rope_cs(pos, a.inv_freq[f0 + e], c, sf);
-            r[e] = second ? acc[e] * c + partner * sf : acc[e] * c - partner * sf;
+            const float2 cs = s_cs[e][lane];
+            r[e] = second ? acc[e] * cs.x + partner * cs.y : acc[e] * cs.x - partner * cs.y;
         }
         dst = head < a.H ? a.q + ((int64_t)j * a.H + head) * hd + i0
                          : a.kc + ((int64_t)(head - a.H) * a.max_seq + pos) * hd + i0;
