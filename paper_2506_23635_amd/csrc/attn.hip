@@ -809,6 +809,15 @@ __device__ inline f32x16_t mfma32x32x16(const u32x4_t a, const u32x4_t b, f32x16
                                                    __builtin_bit_cast(moe::bf16x8_t, b), c, 0, 0, 0);
 }
 
+// A maximum in base 2, with the product's one rounding everywhere: p, the
+// rescaling and the merges then refer to the same value, and its rounding
+// cancels (contracted into a difference it would not).
+__device__ inline float base2(float m, float scale2)
+{
+#pragma clang fp contract(off)
+    return m * scale2;
+}
+
 constexpr int flash_rows(int pg) { return 128 / pg; }        // query rows per workgroup
 constexpr int kFlashP = 64;                                  // positions per step
 
@@ -989,7 +998,7 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
         const float mn = fmaxf(m, mx);
         // a row with every position masked so far keeps mn = -inf: subtract
         // 0 instead, so its p are 0, not NaN
-        const float msub = mn == -INFINITY ? 0.f : -mn * a.scale2;
+        const float ms = base2(mn, a.scale2), msub = mn == -INFINITY ? 0.f : -ms;
         float ps = 0.f;
         float pv[NB * 16];
 #pragma unroll
@@ -1001,7 +1010,7 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
         // rescale the running sums only where a maximum moved (m == mn gives
         // the factor 1 exactly, so skipping it changes no bit)
         if (__ballot(mn != m)) {
-            const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - mn) * a.scale2);
+            const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(base2(m, a.scale2) - ms);
             l *= alpha;
 #pragma unroll
             for (int b = 0; b < DB; ++b) o[b] *= alpha;
@@ -1063,8 +1072,9 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
             const float* src = mg + ((k - 1) * kRowWaves + w) * (DB * 16 + 2) * 64 + lane;
             const float m2 = src[DB * 16 * 64], l2 = src[(DB * 16 + 1) * 64];
             const float mn = fmaxf(m, m2);
-            const float f1 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - mn) * a.scale2);
-            const float f2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m2 - mn) * a.scale2);
+            const float ms = base2(mn, a.scale2);
+            const float f1 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(base2(m, a.scale2) - ms);
+            const float f2 = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(base2(m2, a.scale2) - ms);
 #pragma unroll
             for (int b = 0; b < DB; ++b)
 #pragma unroll
@@ -1085,7 +1095,7 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
                 *reinterpret_cast<float4*>(dst + b * 32 + 8 * g + 4 * h) =
                     make_float4(o[b][4 * g], o[b][4 * g + 1], o[b][4 * g + 2], o[b][4 * g + 3]);
         if (h == 0) {
-            dst[HD] = m * a.scale2;
+            dst[HD] = base2(m, a.scale2);
             dst[HD + 1] = l;
         }
         return;
