@@ -1293,6 +1293,7 @@ int attn_part_stride(int hd) { return hd + attn::kPartPad; }
 // 43.4, 2047 45.4 against 43.7).  At most kShortChunks chunks.
 constexpr int kShortPos = 1024;
 constexpr int kShortChunks = kShortPos / attn::kChunk;
+static_assert(attn::kChunk == attn::kFlashP, "attn_split_max counts both in the same steps");
 
 int attn_short(int T, int H, int G, int n_pos) { return T * (H / G) <= 16 && n_pos <= kShortPos; }
 
@@ -1306,15 +1307,16 @@ static int flash_pg(int T, int H, int G)
     return R <= 64 ? 2 : 1;
 }
 
-// The most position ranges for T new tokens, whatever their positions: at
-// most 1024 workgroups, 2^17 rows of partial sums (69 MB at head_dim 128) and
-// 128 ranges.
-int attn_split_max(int T, int H, int G)
+// The most position ranges (or chunks of score_kernel) for T new tokens,
+// whatever their positions: at most 1024 workgroups, 2^17 rows of partial sums
+// (69 MB at head_dim 128), 128 ranges and the steps of max_seq positions.
+int attn_split_max(int T, int H, int G, int max_seq)
 {
     const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg);
     const int64_t blocks = (int64_t)G * (((int64_t)T * (H / G) + rows - 1) / rows);
-    return (int)std::max<int64_t>(attn_short(T, H, G, 1) ? kShortChunks : 1,
-                                  std::min<int64_t>({1024 / blocks, (1 << 17) / ((int64_t)T * H), 128}));
+    const int64_t most = std::max<int64_t>(attn_short(T, H, G, 1) ? kShortChunks : 1,
+                                           std::min<int64_t>({1024 / blocks, (1 << 17) / ((int64_t)T * H), 128}));
+    return (int)std::min<int64_t>(most, ((int64_t)max_seq + attn::kFlashP - 1) / attn::kFlashP);
 }
 
 // Position ranges for T new tokens at pos0: the count with the least
@@ -1326,12 +1328,12 @@ int attn_split_max(int T, int H, int G)
 // 219 -> 88 us (64 ranges; 32: 89, 128: 103), 64 after 8000 426 -> 123 (32;
 // 16: 134, 64: 141), 300 after 1000 189 -> 161 (4; 2: 168, 8: 169), 512 after
 // 8000 528 -> 367 (5; 2: 385); 1024 from empty 306 (1; 2: 339).
-int attn_split(int T, int H, int G, int pos0)
+int attn_split(int T, int H, int G, int pos0, int max_seq)
 {
     const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg), step = attn::kFlashP;
     const int64_t nrb = ((int64_t)T * (H / G) + rows - 1) / rows;
     const double longest = (double)((pos0 + T + step - 1) / step), shortest = (double)(pos0 / step + 1);
-    const int64_t most = std::min<int64_t>(attn_split_max(T, H, G), (int64_t)longest);
+    const int64_t most = std::min<int64_t>(attn_split_max(T, H, G, max_seq), (int64_t)longest);
     int best = 1;
     double best_cost = 0.0;
     for (int S = 1; S <= most; ++S) {

@@ -88,7 +88,7 @@ Layout make_layout(const attn_config* c)
     // the attention's partial sums over position ranges (none with one range)
     size_t part_rows = 0;
     for (int T = 1; T <= (int)Tm; ++T) {
-        const int n_split = attn_split_max(T, c->n_heads, c->n_kv_heads);
+        const int n_split = attn_split_max(T, c->n_heads, c->n_kv_heads, c->max_seq);
         if (n_split > 1) part_rows = std::max(part_rows, (size_t)T * H * n_split);
     }
     L.part_off = take(part_rows * attn_part_stride((int)hd) * 4);
@@ -215,7 +215,7 @@ moe_status attention(attn_ctx* ctx, int layer, const uint16_t* q, uint16_t* a, i
         if (e != hipSuccess) return hip_fail(ctx, e, "merge kernel launch");
         return MOE_OK;
     }
-    const int n_split = attn_split(T, c.n_heads, c.n_kv_heads, pos0);   // at most attn_split_max
+    const int n_split = attn_split(T, c.n_heads, c.n_kv_heads, pos0, c.max_seq);   // at most attn_split_max
     e = timed(ctx, ATTN_K_SCORE, s, [&] {
         return attn_launch_flash(q, layer_k(ctx, layer), layer_v(ctx, layer), part, a, T, c.n_heads,
                                  c.n_kv_heads, c.head_dim, c.max_seq, pos0, few, n_split, s);
