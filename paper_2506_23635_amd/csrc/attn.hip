@@ -70,10 +70,11 @@ __device__ inline u32x4_t ld16(const void* p) { return *reinterpret_cast<const u
 // 16 tokens after 100 66.8 -> 64.8; three tiles per batch 41.9 and 64.0, but
 // 24.6 against 23.8 at d 2048; six 42.3 and 66.8.)  The loads have no branches (an unused column reads token
 // 0's row and feeds zeros), so a wait for them is not a wait for everything.
+// kS row tiles, `slab` bytes apart, share each token fragment.
 // kt: K tiles done; `meanwhile` runs once while the first loads are in flight.
-template <class F>
-__device__ __forceinline__ void stream_batches(const uint8_t* pw, const uint16_t* px, int nb, int w,
-                                               bool has_tok, f32x4_t& acc, int& kt, F&& meanwhile)
+template <int kS, class F>
+__device__ __forceinline__ void stream_batches(const uint8_t* pw, int64_t slab, const uint16_t* px, int nb,
+                                               int w, bool has_tok, f32x4_t (&acc)[kS], int& kt, F&& meanwhile)
 {
     constexpr int kStep = kSplit * kUnrollX;
     const u32x4_t zero = {0u, 0u, 0u, 0u};
@@ -82,17 +83,22 @@ __device__ __forceinline__ void stream_batches(const uint8_t* pw, const uint16_t
         for (int u = 0; u < kUnrollX; ++u) xv[u] = ld16(px + (b * kStep + w + kSplit * u) * kTileK);
 #pragma unroll
         for (int u = 0; u < kUnrollX; ++u)
-            wt[u] = ld16_nt(pw + (int64_t)(b * kStep + w + kSplit * u) * kTileBytes);
+#pragma unroll
+            for (int c = 0; c < kS; ++c)
+                wt[u * kS + c] = ld16_nt(pw + c * slab + (int64_t)(b * kStep + w + kSplit * u) * kTileBytes);
     };
     auto mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
 #pragma unroll
-        for (int u = 0; u < kUnrollX; ++u) acc = moe::mfma16x16x32(wt[u], has_tok ? xv[u] : zero, acc);
+        for (int u = 0; u < kUnrollX; ++u)
+#pragma unroll
+            for (int c = 0; c < kS; ++c)
+                acc[c] = moe::mfma16x16x32(wt[u * kS + c], has_tok ? xv[u] : zero, acc[c]);
     };
     if (nb == 0) {
         meanwhile();
         return;
     }
-    u32x4_t wa[kUnrollX], wb[kUnrollX], xa[kUnrollX], xb[kUnrollX];
+    u32x4_t wa[kUnrollX * kS], wb[kUnrollX * kS], xa[kUnrollX], xb[kUnrollX];
     load(0, wa, xa);
     meanwhile();
     int b = 0;
@@ -113,7 +119,7 @@ __device__ __forceinline__ void stream_batches(const uint8_t* pw, const uint16_t
 }
 
 // The output projection, o = a Wo (fp32) and y = bf16(x + o), one
-// workgroup per 16 output features.
+// workgroup per kS tiles of 16 output features (two_tiles).
 struct GemvArgs {
     const uint8_t* w;      // packed weights: N/16 row tiles of K/32 tiles
     const uint16_t* x;     // [T][K] bf16
@@ -123,41 +129,48 @@ struct GemvArgs {
     int K, N, T;
 };
 
+template <int kS>
 __global__ __launch_bounds__(64 * kSplit) void gemv_kernel(GemvArgs a)
 {
-    __shared__ f32x4_t s_red[(kSplit - 1) * 64];
-    const int q = blockIdx.x;                   // output features 16q .. 16q+15
+    __shared__ f32x4_t s_red[kS][kSplit * 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int q = blockIdx.x * kS;             // row tiles q .. q + kS - 1
     const int j = lane & 15, g = lane >> 4;    // token column, K group of 8
     const int KT = a.K / kTileK;
+    const int64_t slab = (int64_t)KT * kTileBytes;
     const uint8_t* pw = a.w + moe::tile_offset(q, 0, KT) + lane * 16;
     const bool has_tok = j < a.T;
     const uint16_t* px = a.x + (has_tok ? (int64_t)j * a.K : 0) + g * 8;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc[kS] = {};
     const u32x4_t zero = {0u, 0u, 0u, 0u};
-    // the residual of the lane's outputs, loaded ahead of the weights (output
-    // features 16q + 4g .. +3 of token j; other lanes read token 0's)
-    const int64_t o = (int64_t)(has_tok ? j : 0) * a.N + q * kTileRows + g * 4;
+    // wave c < kS ends row tile q + c.  The residual of its lanes' outputs,
+    // loaded ahead of the weights (output features 16 (q + c) + 4g .. +3 of
+    // token j; other lanes read token 0's)
+    const int c = min(w, kS - 1);
+    const int64_t o = (int64_t)(has_tok ? j : 0) * a.N + (q + c) * kTileRows + g * 4;
     const uint2 r = *reinterpret_cast<const uint2*>(a.res + o);
     int kt = 0;
-    stream_batches(pw, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, [] {});
+    stream_batches<kS>(pw, slab, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, [] {});
     for (kt += w; kt < KT; kt += kSplit) {
-        const u32x4_t wt = ld16_nt(pw + (int64_t)kt * kTileBytes);
         const u32x4_t xt = has_tok ? ld16(px + kt * kTileK) : zero;
-        acc = moe::mfma16x16x32(wt, xt, acc);
+#pragma unroll
+        for (int i = 0; i < kS; ++i)
+            acc[i] = moe::mfma16x16x32(ld16_nt(pw + i * slab + (int64_t)kt * kTileBytes), xt, acc[i]);
     }
-    if (w > 0) s_red[(w - 1) * 64 + lane] = acc;
+#pragma unroll
+    for (int i = 0; i < kS; ++i) s_red[i][w * 64 + lane] = acc[i];
     __syncthreads();
-    if (w != 0) return;
-    for (int i = 0; i + 1 < kSplit; ++i) acc += s_red[i * 64 + lane];
+    if (w >= kS) return;
+    f32x4_t sum = s_red[c][lane];
+    for (int i = 1; i < kSplit; ++i) sum += s_red[c][i * 64 + lane];
     if (!has_tok) return;
-    *reinterpret_cast<float4*>(a.y32 + o) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    *reinterpret_cast<float4*>(a.y32 + o) = make_float4(sum[0], sum[1], sum[2], sum[3]);
     const float r0 = __uint_as_float(r.x << 16), r1 = __uint_as_float(r.x & 0xFFFF0000u);
     const float r2 = __uint_as_float(r.y << 16), r3 = __uint_as_float(r.y & 0xFFFF0000u);
-    const uint32_t lo = (uint32_t)moe::f32_to_bf16(r0 + acc[0]) |
-                        ((uint32_t)moe::f32_to_bf16(r1 + acc[1]) << 16);
-    const uint32_t hi = (uint32_t)moe::f32_to_bf16(r2 + acc[2]) |
-                        ((uint32_t)moe::f32_to_bf16(r3 + acc[3]) << 16);
+    const uint32_t lo = (uint32_t)moe::f32_to_bf16(r0 + sum[0]) |
+                        ((uint32_t)moe::f32_to_bf16(r1 + sum[1]) << 16);
+    const uint32_t hi = (uint32_t)moe::f32_to_bf16(r2 + sum[2]) |
+                        ((uint32_t)moe::f32_to_bf16(r3 + sum[3]) << 16);
     *reinterpret_cast<uint2*>(a.y16 + o) = make_uint2(lo, hi);
 }
 
@@ -289,37 +302,41 @@ constexpr int kHPad = 8;       // bf16 padding of a token row of h in LDS
 // then x and x^2 summed in fp64 (butterfly per wave, the 8 waves in order),
 // h = bf16((x - mean) rstd gamma) to LDS (workgroup 0 also writes it out);
 // the main loop then reads its B fragments from LDS.  Otherwise h comes from
-// norm_kernel through global memory.
-template <bool kNorm>
+// norm_kernel through global memory, and each fragment serves kS row tiles.
+template <bool kNorm, int kS>
 __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
 {
-    __shared__ f32x4_t s_red[(kSplit - 1) * 64];
+    static_assert(kS == 1 || (kS == 2 && !kNorm && kSplit == 8));
+    __shared__ f32x4_t s_red[kS][kSplit * 64];
     extern __shared__ __attribute__((aligned(16))) uint16_t hs[];   // kNorm: [T][d + kHPad]
-    const int q = blockIdx.x;
+    const int q = blockIdx.x * kS;             // row tiles q .. q + kS - 1
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int KT = a.d / kTileK;
     const int hstride = a.d + kHPad;
+    const int64_t slab = (int64_t)KT * kTileBytes;
     const uint8_t* pw = a.w + moe::tile_offset(q, 0, KT) + lane * 16;
     const bool has_tok = j < a.T;
     const uint16_t* px = a.h + (has_tok ? (int64_t)j * a.d : 0) + g * 8;
     const uint16_t* hx = hs + (has_tok ? j * hstride : 0) + g * 8;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc[kS] = {};
     const u32x4_t zero = {0u, 0u, 0u, 0u};
     u32x4_t wv[kUnroll], xb[kUnroll];
-    // the rotations that the epilogue applies, formed while the first weights
-    // are in flight (in the epilogue they were a chain of their own behind
-    // the stream): wave e < 4 forms those of the lanes' e-th pairs
-    __shared__ float2 s_cs[4][64];
-    const int row0 = q * kTileRows, nqk_rows = (a.H + a.G) * a.hd;
-    const bool turn = row0 < nqk_rows;
-    const int fr = 8 * ((row0 % a.hd) / kTileRows) + 4 * (g & 1) + (w & 3);   // frequency of wave w's pair
+    // wave c < kS ends row tile q + c.  The rotations that it applies are
+    // formed while the first weights are in flight (in the epilogue they were
+    // a chain of their own behind the stream): wave 4 c + e forms those of
+    // the lanes' e-th pairs
+    __shared__ float2 s_cs[kS][4][64];
+    const int nqk_rows = (a.H + a.G) * a.hd;
+    const int rc = min(w / 4, kS - 1), rrow = (q + rc) * kTileRows;
+    const bool turn = rrow < nqk_rows && w < 4 * kS;
+    const int fr = 8 * ((rrow % a.hd) / kTileRows) + 4 * (g & 1) + (w & 3);   // frequency of wave w's pair
     const double inv_fr = a.inv_freq[turn ? fr : 0];
     auto rotations = [&] {
-        if (turn && w < 4) {
+        if (turn) {
             float c, sf;
             rope_cs(a.pos0 + j, inv_fr, c, sf);
-            s_cs[w][lane] = make_float2(c, sf);
+            s_cs[rc][w & 3][lane] = make_float2(c, sf);
         }
     };
     if constexpr (kNorm) {
@@ -400,7 +417,7 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
     }
     int kt = 0;
     if constexpr (!kNorm) {
-        stream_batches(pw, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, rotations);
+        stream_batches<kS>(pw, slab, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, rotations);
     } else {
         // two weight buffers in turn (the first batch was issued above, into
         // wv), tokens from LDS
@@ -420,7 +437,7 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
         };
         auto mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) acc = moe::mfma16x16x32(wt[u], xv[u], acc);
+            for (int u = 0; u < kUnroll; ++u) acc[0] = moe::mfma16x16x32(wt[u], xv[u], acc[0]);
         };
         if (nb > 0) {
             u32x4_t wb[kUnroll];
@@ -446,19 +463,23 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
         }
     }
     for (kt += w; kt < KT; kt += kSplit) {
-        const u32x4_t wt = ld16_nt(pw + (int64_t)kt * kTileBytes);
         u32x4_t xt;
         if constexpr (kNorm)
             xt = has_tok ? *reinterpret_cast<const u32x4_t*>(hx + kt * kTileK) : zero;
         else
             xt = has_tok ? ld16(px + kt * kTileK) : zero;
-        acc = moe::mfma16x16x32(wt, xt, acc);
+#pragma unroll
+        for (int i = 0; i < kS; ++i)
+            acc[i] = moe::mfma16x16x32(ld16_nt(pw + i * slab + (int64_t)kt * kTileBytes), xt, acc[i]);
     }
-    if (w > 0) s_red[(w - 1) * 64 + lane] = acc;
+#pragma unroll
+    for (int i = 0; i < kS; ++i) s_red[i][w * 64 + lane] = acc[i];
     __syncthreads();
-    if (w != 0) return;
-    for (int i = 0; i + 1 < kSplit; ++i) acc += s_red[i * 64 + lane];
+    if (w >= kS) return;
+    f32x4_t sum = s_red[w][lane];
+    for (int i = 1; i < kSplit; ++i) sum += s_red[w][i * 64 + lane];
     if (!has_tok) return;
+    const int row0 = (q + w) * kTileRows;
     const int hd = a.hd, half = hd / 2;
     const int nqk = (a.H + a.G) * hd, nqkv = nqk + a.G * hd;
     const int pos = a.pos0 + j;
@@ -468,22 +489,22 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
     if (row0 < nqk) {
         const int head = row0 / hd, m = (row0 % hd) / kTileRows;
         const bool second = g >= 2;
-        const int f0 = 8 * m + 4 * (g & 1);           // frequency index of acc[0]
+        const int f0 = 8 * m + 4 * (g & 1);           // frequency index of sum[0]
         const int i0 = (second ? half : 0) + f0;       // feature index in the head
-        *reinterpret_cast<float4*>(qrow + head * hd + i0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        *reinterpret_cast<float4*>(qrow + head * hd + i0) = make_float4(sum[0], sum[1], sum[2], sum[3]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float partner = __shfl_xor(acc[e], 32, 64);
-            const float2 cs = s_cs[e][lane];
-            r[e] = second ? acc[e] * cs.x + partner * cs.y : acc[e] * cs.x - partner * cs.y;
+            const float partner = __shfl_xor(sum[e], 32, 64);
+            const float2 cs = s_cs[w][e][lane];
+            r[e] = second ? sum[e] * cs.x + partner * cs.y : sum[e] * cs.x - partner * cs.y;
         }
         dst = head < a.H ? a.q + ((int64_t)j * a.H + head) * hd + i0
                          : a.kc + ((int64_t)(head - a.H) * a.max_seq + pos) * hd + i0;
     } else {
         const int n = row0 + 4 * g;                    // value features: natural order
-        *reinterpret_cast<float4*>(qrow + n) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        *reinterpret_cast<float4*>(qrow + n) = make_float4(sum[0], sum[1], sum[2], sum[3]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = acc[e];
+        for (int e = 0; e < 4; ++e) r[e] = sum[e];
         dst = a.vc + ((int64_t)((n - nqk) / hd) * a.max_seq + pos) * hd + (n - nqk) % hd;
     }
     const uint32_t lo = (uint32_t)moe::f32_to_bf16(r[0]) | ((uint32_t)moe::f32_to_bf16(r[1]) << 16);
@@ -1248,6 +1269,15 @@ hipError_t attn_launch_norm(const uint16_t* x, const float* gamma, int T, int d,
 
 int attn_norm_in_projection(int T) { return T <= attn::kLnMaxT; }
 
+// Two row tiles per workgroup in the decode projections: each token fragment,
+// as many bytes as a weight tile's and read by every workgroup, then serves
+// two tiles.  It pays where the halved grid still covers three quarters of the
+// CUs (16 tokens: 512 + 384 tiles 63.9 -> 55.3 us for the block, 384 of q|k|v
+// alone 39.1 -> 38.1; 256 of the output alone 39.1 -> 41.7, 192 of q|k|v 23.8
+// -> 25.0, 128 of the output 23.8 -> 25.4).  One token, whose q|k|v reads its
+// fragments from LDS: the output projection alone 41.3 -> 40.5.
+static bool two_tiles(int tiles) { return tiles >= 384 && tiles % 2 == 0; }
+
 hipError_t attn_launch_qkv(const void* w, uint16_t* h, const uint16_t* x, const float* gamma,
                            float eps, const double* inv_freq, float* qkv, uint16_t* q,
                            uint16_t* kc, uint16_t* vc, int T, int d, int H, int G, int hd,
@@ -1259,9 +1289,11 @@ hipError_t attn_launch_qkv(const void* w, uint16_t* h, const uint16_t* x, const 
     const dim3 grid(rows / moe::kTileRows), block(64 * attn::kSplit);
     if (attn_norm_in_projection(T)) {
         const size_t lds = (size_t)T * (d + attn::kHPad) * 2;
-        hipLaunchKernelGGL(attn::qkv_kernel<true>, grid, block, lds, s, a);
+        hipLaunchKernelGGL((attn::qkv_kernel<true, 1>), grid, block, lds, s, a);
     } else {
-        hipLaunchKernelGGL(attn::qkv_kernel<false>, grid, block, 0, s, a);
+        // (H + 2 G) hd is a multiple of 64: the row tiles are even in number
+        if (two_tiles(grid.x)) hipLaunchKernelGGL((attn::qkv_kernel<false, 2>), dim3(grid.x / 2), block, 0, s, a);
+        else hipLaunchKernelGGL((attn::qkv_kernel<false, 1>), grid, block, 0, s, a);
     }
     return hipGetLastError();
 }
@@ -1270,7 +1302,10 @@ hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N
                            const uint16_t* res, uint16_t* y16, hipStream_t s)
 {
     attn::GemvArgs a{static_cast<const uint8_t*>(w), x, y32, res, y16, K, N, T};
-    hipLaunchKernelGGL(attn::gemv_kernel, dim3(N / moe::kTileRows), dim3(64 * attn::kSplit), 0, s, a);
+    const int tiles = N / moe::kTileRows;
+    const dim3 block(64 * attn::kSplit);
+    if (two_tiles(tiles)) hipLaunchKernelGGL(attn::gemv_kernel<2>, dim3(tiles / 2), block, 0, s, a);
+    else hipLaunchKernelGGL(attn::gemv_kernel<1>, dim3(tiles), block, 0, s, a);
     return hipGetLastError();
 }
 

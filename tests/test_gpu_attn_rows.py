@@ -37,3 +37,26 @@ def test_row_and_range_edges(torch_mod, H, G, hd, T, pos0):  # noqa: F811
         assert (case.forward(x, pos0) == y).all()
     finally:
         case.close()
+
+
+# the decode projections take two row tiles per workgroup from 384 tiles on
+# (q|k|v: (H + 2G) hd / 16 tiles over d; output: d / 16 tiles over H hd), in
+# batches of 32 K tiles of 32
+@pytest.mark.parametrize("d,H,G,hd,T,pos0", [
+    (512, 60, 15, 64, 16, 0),      # q|k|v 360 tiles: one per workgroup
+    (512, 32, 8, 128, 16, 70),     # 384 tiles: two, heads of both halves; half a batch of K
+    (1280, 32, 8, 128, 5, 1500),   # one batch and a remainder
+    (6144, 36, 6, 64, 9, 30),      # output 384 tiles, two batches and a remainder
+    (6144, 4, 4, 64, 1, 3),        # one token: output in pairs, less than a batch
+])
+def test_projection_tile_pairs(torch_mod, d, H, G, hd, T, pos0):  # noqa: F811
+    wl = TINY.with_(d=d, n_heads=H, n_kv=G, hd=hd, T=T, pos0=pos0, max_seq=2048)
+    case = Case(torch_mod, wl, max_tokens=16)
+    try:
+        x = wl.x()
+        y = case.forward(x, pos0)
+        kc, vc = case.cache()
+        check_block(case, x, pos0, y, case.layer.intermediates(T), kc, vc)
+        assert (case.forward(x, pos0) == y).all()
+    finally:
+        case.close()
