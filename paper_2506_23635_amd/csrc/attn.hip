@@ -22,14 +22,15 @@
 //   gemv_kernel     o = a Wo (fp32) and y = bf16(x + o)
 //
 // Above 16 new tokens (prefill) the block is: norm_kernel -> q|k|v on the
-// grouped GEMM of moe_prefill.hip -> rope_kernel (rotation, cache append)
+// grouped GEMM of moe_prefill.hip, rotation and cache append in its end
 // -> flash_kernel (and merge_kernel or merge_few_kernel) -> o = a Wo on the
-// grouped GEMM -> residual_kernel.
+// grouped GEMM, the residual in its end.  Where those reductions are split,
+// rope_kernel and residual_kernel add the parts and do the ends' work.
 //
 // The GEMVs stream the fragment-tiled weights (the layout of moe_common.h)
 // through v_mfma_f32_16x16x32_bf16 with the tokens as the B operand, as the
-// MoE decode GEMVs do: one workgroup per 16 output features, its 8 waves
-// splitting K (wave w takes K tiles w, w + 8, ...), wave 0 adding the
+// MoE decode GEMVs do: one workgroup per 16 output features (or 32, see
+// two_tiles), its 8 waves splitting K (wave w takes K tiles w, w + 8, ...), wave 0 adding the
 // partial fragments in wave order.
 #include <algorithm>
 #include <cmath>
