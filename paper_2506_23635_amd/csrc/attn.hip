@@ -1346,13 +1346,21 @@ static int flash_pg(int T, int H, int G)
 // The most position ranges (or chunks of score_kernel) for T new tokens,
 // whatever their positions: at most 1024 workgroups, 2^17 rows of partial sums
 // (69 MB at head_dim 128), 128 ranges and the steps of max_seq positions.
-int attn_split_max(int T, int H, int G, int max_seq)
+static int attn_split_max(int T, int H, int G, int max_seq)
 {
     const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg);
     const int64_t blocks = (int64_t)G * (((int64_t)T * (H / G) + rows - 1) / rows);
     const int64_t most = std::max<int64_t>(attn_short(T, H, G, 1) ? kShortChunks : 1,
                                            std::min<int64_t>({1024 / blocks, (1 << 17) / ((int64_t)T * H), 128}));
     return (int)std::min<int64_t>(most, ((int64_t)max_seq + attn::kFlashP - 1) / attn::kFlashP);
+}
+
+// The most ranges or chunks whose partial sums a call of T new tokens stores:
+// score_kernel stores them with one chunk too, flash_kernel from two ranges on.
+int attn_part_max(int T, int H, int G, int max_seq)
+{
+    const int most = attn_split_max(T, H, G, max_seq);
+    return most > 1 || attn_short(T, H, G, 1) ? most : 0;
 }
 
 // Position ranges for T new tokens at pos0: the count with the least

@@ -85,12 +85,10 @@ Layout make_layout(const attn_config* c)
     L.h_off = take(Tm * d * 2);
     L.qkv_off = take(Tm * L.nqkv * 4);
     L.q_off = take(Tm * L.nq * 2);
-    // the attention's partial sums over position ranges (none with one range)
+    // the attention's partial sums over position ranges
     size_t part_rows = 0;
-    for (int T = 1; T <= (int)Tm; ++T) {
-        const int n_split = attn_split_max(T, c->n_heads, c->n_kv_heads, c->max_seq);
-        if (n_split > 1) part_rows = std::max(part_rows, (size_t)T * H * n_split);
-    }
+    for (int T = 1; T <= (int)Tm; ++T)
+        part_rows = std::max(part_rows, T * H * attn_part_max(T, c->n_heads, c->n_kv_heads, c->max_seq));
     L.part_off = take(part_rows * attn_part_stride((int)hd) * 4);
     L.a_off = take(Tm * L.nq * 2);
     L.o_off = take(Tm * d * 4);

@@ -203,7 +203,7 @@ hipError_t attn_launch_short(const uint16_t* q, const uint16_t* kc, const uint16
                              int T, int H, int G, int hd, int max_seq, int pos0, hipStream_t s);
 hipError_t attn_launch_short_merge(const float* part, uint16_t* out, int T, int H, int hd, int pos0,
                                    hipStream_t s);
-int attn_split_max(int T, int H, int G, int max_seq);
+int attn_part_max(int T, int H, int G, int max_seq);
 int attn_split(int T, int H, int G, int pos0, int max_seq);
 hipError_t attn_launch_flash(const uint16_t* q, const uint16_t* kc, const uint16_t* vc, float* part,
                              uint16_t* out, int T, int H, int G, int hd, int max_seq, int pos0,

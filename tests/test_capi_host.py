@@ -270,6 +270,22 @@ def test_attn_sizes():
     assert moe.attn_workspace_bytes(cfg) > 16 * (6144 * 2 + 8192 * 4)
 
 
+@pytest.mark.parametrize("max_seq", [1, 63, 64, 65, 128, 1024, 1025])
+@pytest.mark.parametrize("H,G,hd", [(8, 1, 128), (16, 2, 64), (32, 8, 128), (48, 8, 128), (8, 8, 64), (16, 8, 128)])
+def test_attn_workspace_holds_the_chunks_partial_sums(max_seq, H, G, hd):
+    """Calls of up to 16 query rows per key/value head and 1024 positions store
+    head_dim + 4 floats per token, head and chunk of 64 positions, also with
+    one chunk: what the workspace holds beside its other buffers (h, q|k|v, q,
+    attention output, o; padded to 256 bytes each) has room for them."""
+    d, nq, nqkv = 256, H * hd, (H + 2 * G) * hd
+    for T_max in (1, 2, 4, 16):
+        cfg = _attn_cfg(d_model=d, n_heads=H, n_kv_heads=G, head_dim=hd, max_seq=max_seq, max_tokens=T_max)
+        others = sum((T_max * n + 255) // 256 * 256 for n in (d * 2, nqkv * 4, nq * 2, nq * 2, d * 4))
+        rows = max([T * H * ((min(max_seq, 1024) + 63) // 64)
+                    for T in range(1, min(T_max, max_seq) + 1) if T * (H // G) <= 16], default=0)
+        assert moe.attn_workspace_bytes(cfg) - others >= rows * (hd + 4) * 4, (T_max, rows)
+
+
 @pytest.mark.parametrize("bad", [dict(d_model=200), dict(d_model=8448), dict(head_dim=96), dict(n_kv_heads=5),
                                  dict(n_heads=64, n_kv_heads=4), dict(max_tokens=32769),
                                  dict(n_heads=4, n_kv_heads=1, head_dim=64, max_tokens=17),

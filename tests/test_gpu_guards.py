@@ -212,3 +212,33 @@ def test_attention_stays_inside_its_buffers(torch_mod, T, pos0):
         assert not np.all(kv[:, :, pos0:pos0 + T] == 0x5A)
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("T,max_tokens,max_seq", [(2, 2, 64), (1, 1, 1), (2, 16, 63)])
+def test_attention_in_a_cache_of_one_chunk(torch_mod, T, max_tokens, max_seq):
+    """One chunk of positions: its partial sums still go through the
+    workspace (8 heads over one key/value head and d 256, where they are larger
+    than all that follows them there).  The margins hold, and every stage
+    checks per element."""
+    import paper_2506_23635_amd as moe
+    from test_gpu_attn import Case, check_block
+    torch = torch_mod
+    aw = ATTN.with_(T=T, pos0=max_seq - T, d=256, n_heads=8, n_kv=1, hd=128, max_seq=max_seq)
+    case = Case(torch, aw, max_tokens=max_tokens)
+    cfg = case.layer.cfg
+    ws = Guarded(torch, moe.attn_workspace_bytes(cfg))
+    arena, cache = case.layer.arena, case.layer.cache
+    case.layer.close()
+    case.layer = moe.AttnLayer(cfg, arena=arena, cache=cache, workspace=ws.inner)
+    try:
+        case.layer.load_layer(0, torch.from_numpy(case.gamma), torch.from_numpy(case.wqkv.view(np.int16)),
+                              torch.from_numpy(case.wo.view(np.int16)))
+        x = aw.x()
+        y = case.forward(x, aw.pos0)
+        kc, vc = case.cache()
+        check_block(case, x, aw.pos0, y, case.layer.intermediates(T), kc, vc)
+        assert ws.intact()
+        for _ in range(5):
+            assert np.array_equal(case.forward(x, aw.pos0), y)
+    finally:
+        case.close()
