@@ -646,6 +646,25 @@ __device__ __forceinline__ void write_stamp(const GemmArgs& a, uint64_t r0, uint
 // an XCD, which deals its blocks to its shader engines and CUs in turn,
 // left up to half of them without a live one (237 workgroups running at a
 // time of the 512 that fit).
+//
+// The feature tiles left over from the groups of eight are dealt in runs of
+// consecutive token tiles, whose lengths go on from expert to expert so that
+// the XCDs' shares of all tiles differ by one at most.  (Where feature tile ft
+// always went to XCD ft % 8, the XCDs past the remainder had nothing of it: 4
+// experts of d 2304, f 1152, 9 and 9 tiles of 256 features, 8000 tokens, gate/up
+// and down 215 + 143 us, so 174 + 120; on DBRX's gate/up, 84 tiles, a share of 4
+// experts with skewed loads, 1300 tokens, whole layer 587 -> 550 us.)
+//
+// Narrow matrices (below 2048 features) are one list of the experts' tiles, an
+// eighth of it for each XCD, so that most experts' weights and token rows are
+// read through one L2 (dealt as above every XCD reads every expert's: 32 experts
+// of d 512, f 4096, 4000 tokens, down 149 us against 103; 16 of d 1024, f 4096,
+// 1900 tokens, 112 against 98).  At 2048 features and more the XCDs stay with one
+// expert at a time (8 experts of d 2048, f 8192, 4000 tokens, down 304 us
+// against 354 from a list).  Whole layer, 8 experts, top-2, d 256, f 512, 32768
+// tokens: 505 us with tile ft on XCD ft % 8, now 335.
+constexpr int kNarrow = 2048;      // features
+
 struct TilePos {
     int el;            // local expert, or -1 past the last tile
     int first, rows;   // its rows
@@ -655,8 +674,9 @@ struct TilePos {
 
 __device__ __forceinline__ TilePos find_tile(const GemmArgs& a, int block, int n_ftiles, int tile_rows)
 {
-    const int n_fg = (n_ftiles + kXcds - 1) / kXcds;
-    const int pos = block / kXcds;
+    // groups of eight, and the rest
+    const int n_fg = n_ftiles * tile_rows < kNarrow ? 0 : n_ftiles / kXcds, n_left = n_ftiles - n_fg * kXcds;
+    const int pos = block / kXcds, xcd = block % kXcds;
     const int lane = threadIdx.x & 63;
     int first = 0, rows = 0;
     if (a.offsets == nullptr) {              // a plain product: T rows
@@ -672,15 +692,37 @@ __device__ __forceinline__ TilePos find_tile(const GemmArgs& a, int block, int n
         const int v = __shfl_up(upto, off, kWave);
         if (lane >= off) upto += v;
     }
+    // this XCD's tiles of the first n token tiles where there are whole
+    // groups: those of the groups, and of the n n_left others every eighth
+    auto taken = [&](int n) { return n * n_fg + (n * n_left + kXcds - 1 - xcd) / kXcds; };
+    // without: its eighth of the list of all tiles
+    const int all = __builtin_amdgcn_readlane(upto, kWave - 1) * n_left;
+    const int at = all * xcd / kXcds + pos;
     TilePos t{};
-    t.el = __ffsll((unsigned long long)__ballot(pos / n_fg < upto)) - 1;
+    t.el = -1;
+    if (n_fg == 0 && at >= all * (xcd + 1) / kXcds) return t;
+    t.el = __ffsll((unsigned long long)__ballot(n_fg ? pos < taken(upto) : at < upto * n_left)) - 1;
     if (t.el < 0) return t;
     t.first = __builtin_amdgcn_readlane(first, t.el);
     t.rows = __builtin_amdgcn_readlane(rows, t.el);
     t.n_sub = __builtin_amdgcn_readlane(n_sub, t.el);
-    const int in_e = pos - (__builtin_amdgcn_readlane(upto, t.el) - t.n_sub) * n_fg;
-    t.sub = in_e % t.n_sub;
-    t.ft = in_e / t.n_sub * kXcds + block % kXcds;
+    const int before = __builtin_amdgcn_readlane(upto, t.el) - t.n_sub;
+    int in_left = at - before * n_left;
+    if (n_fg) {
+        const int in_e = pos - taken(before);
+        if (in_e < t.n_sub * n_fg) {
+            t.sub = in_e % t.n_sub;
+            t.ft = in_e / t.n_sub * kXcds + xcd;
+            return t;
+        }
+        // the left-over tiles as eight runs, the first for the XCD on which
+        // the expert before it ended
+        const int q = (xcd + kXcds * n_left - before % kXcds * n_left) % kXcds;
+        const int run = t.n_sub * n_left / kXcds, longer = t.n_sub * n_left % kXcds;
+        in_left = q * run + min(q, longer) + in_e - t.n_sub * n_fg;
+    }
+    t.sub = in_left % t.n_sub;
+    t.ft = n_fg * kXcds + in_left / t.n_sub;
     return t;
 }
 
@@ -691,7 +733,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmArgs a)
     const int M = kMode == kGateUp ? 2 * a.f : a.d;   // a multiple of BM
     const int n_ftiles = M / BM;
     const TilePos tp = find_tile(a, blockIdx.x, n_ftiles, BN);
-    if (tp.el < 0 || tp.ft >= n_ftiles) return;
+    if (tp.el < 0) return;
     const int ft = tp.ft, tt = tp.sub, e = a.e_begin + tp.el;
     const int row_start = tp.first + tp.sub * BN, row_end = min(row_start + BN, tp.first + tp.rows);
     const bool stamp = a.stamps != nullptr && (int)blockIdx.x < a.max_stamps;
@@ -849,7 +891,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_mid_kernel(GemmArgs a)
     const TilePos tp = find_tile(a, blockIdx.x, n_ftiles * a.k_split, MBN);
     if (tp.el < 0) return;
     const int split = tp.ft / n_ftiles, ft = tp.ft % n_ftiles;
-    if (split >= a.k_split) return;
     const int e = a.e_begin + tp.el;
     // an expert's 32-token blocks spread evenly over its token tiles
     const int per_sub = ((tp.rows + 31) / 32 + tp.n_sub - 1) / tp.n_sub * 32;
@@ -947,19 +988,21 @@ int moe_gemm_plain_split(int T, int M)
 
 }  // extern "C"
 
-// Token tiles of tile_rows rows that a call can have: full ones and one
-// partial tile per expert.
-static int launch_tiles(const moe::GemmArgs* a, int tile_rows)
+// The grid for n_ft feature tiles (times ranges of K): the token tiles of
+// tile_rows rows that a call can have are the full ones and one partial tile
+// per expert, and each XCD takes an eighth of all tiles.
+static dim3 gemm_grid(const moe::GemmArgs* a, int n_ft, int tile_rows)
 {
-    return std::min(a->max_rows, a->max_rows / tile_rows + a->n_local);
+    const int n = std::min(a->max_rows, a->max_rows / tile_rows + a->n_local) * n_ft;
+    return dim3((n + moe::kXcds - 1) / moe::kXcds * moe::kXcds);
 }
 
 template <int kMode>
 static hipError_t launch_gemm(const moe::GemmArgs* a, hipStream_t s)
 {
     const int M = kMode == moe::kGateUp ? 2 * a->f : a->d;
-    const int grid = launch_tiles(a, moe::BN) * ((M / moe::BM + moe::kXcds - 1) / moe::kXcds) * moe::kXcds;
-    hipLaunchKernelGGL((moe::gemm_kernel<kMode>), dim3(grid), dim3(moe::kThreads), 0, s, *a);
+    hipLaunchKernelGGL((moe::gemm_kernel<kMode>), gemm_grid(a, M / moe::BM, moe::BN), dim3(moe::kThreads),
+                       0, s, *a);
     return hipGetLastError();
 }
 
@@ -967,10 +1010,7 @@ template <int kMode>
 static hipError_t launch_gemm_mid(const moe::GemmArgs* a, hipStream_t s)
 {
     const int M = kMode == moe::kGateUp ? 2 * a->f : a->d;
-    const int n_ft = M / moe::MBM * a->k_split;
-    const int grid = launch_tiles(a, moe::MBN) *
-                     ((n_ft + moe::kXcds - 1) / moe::kXcds) * moe::kXcds;
-    hipLaunchKernelGGL((moe::gemm_mid_kernel<kMode>), dim3(grid),
+    hipLaunchKernelGGL((moe::gemm_mid_kernel<kMode>), gemm_grid(a, M / moe::MBM * a->k_split, moe::MBN),
                        dim3(moe::kThreads), 0, s, *a);
     return hipGetLastError();
 }

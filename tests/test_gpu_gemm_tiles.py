@@ -62,3 +62,38 @@ def test_loads_at_tile_edges(torch_mod, d, f, loads):
     check_chain(x, rt, H, O, y, {"y64": y64, "y16": y16, "hb": hb, "w": w},
                 lambda e: (G[e], U[e], D[e]))
     layer.close()
+
+
+@pytest.mark.parametrize("d,f,loads", [(256, 640, (300, 0, 2600, 257)),      # 5 and 1 feature tiles
+                                       (768, 1152, (1, 700, 256, 1024)),     # 9 and 3
+                                       (2816, 1408, (513, 40, 255, 300))])   # 11 and 11
+def test_tiles_are_dealt_evenly_over_the_xcds(torch_mod, d, f, loads):
+    """Whatever the number of feature tiles, every tile is taken once and the
+    XCDs (block b runs on XCD b % 8) get the same number of them, one more or
+    less."""
+    torch = torch_mod
+    n_exp = len(loads)
+    wl = mi.WORKLOADS["tiny"].with_(T=sum(loads), d=d, f=f, E=n_exp, k=1, sigma_w=0.05)
+    layer = make_layer(wl)
+    load_workload_host(layer, wl)
+    x_t, _ = x_device(wl)
+    lg = np.zeros((wl.T, n_exp), np.float32)
+    lg[np.arange(wl.T), np.repeat(np.arange(n_exp), loads)] = 4.0
+    n = 1024
+    bufs = [torch.zeros(n * 8, dtype=torch.int64, device="cuda") for _ in range(2)]
+    moe.moe_profile_gemm_timeline(layer.ctx, bufs[0].data_ptr(), bufs[1].data_ptr(), n)
+    rt = layer.route(0, x_t, logits_in=torch.from_numpy(lg).cuda())
+    layer.forward(0, x_t, torch.empty((wl.T, d), dtype=torch.int16, device="cuda"), routing=rt)
+    torch.cuda.synchronize()
+    token_tiles = sum((c + 255) // 256 for c in loads)
+    for buf, n_ft in ((bufs[0], 2 * f // 256), (bufs[1], d // 256)):
+        t = buf.cpu().numpy().view(np.uint64).reshape(n, 8)
+        live = t[:, 1] > 0
+        what = t[live, 5]
+        assert len(what) == len(np.unique(what)) == token_tiles * n_ft
+        for e, c in enumerate(loads):
+            mine = what[what >> 48 == e]
+            assert int(((mine >> 32) & 0xFFFF).sum()) == c * n_ft
+        per_xcd = np.bincount(np.nonzero(live)[0] % 8, minlength=8)
+        assert per_xcd.max() - per_xcd.min() <= 1, per_xcd
+    layer.close()
