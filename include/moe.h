@@ -297,7 +297,8 @@ MOE_API moe_status moe_profile_read(moe_ctx *ctx, double *total_ms,
  * constant 100 MHz counter at the tile's start and end, [2], [3] the shader
  * clock counter at start and end (so [3]-[2] over ([1]-[0]) / 1e8 s is the
  * clock the tile ran at), [4] HW_ID | XCC_ID << 32 of its CU, [5] feature
- * tile | token tile of the expert << 16 | rows << 32 | expert << 48.  Workgroups without a
+ * tile | token tile << 16 | rows << 32 | expert << 48, token tiles counted
+ * over the local experts in order (MOE_WS_TILES).  Workgroups without a
  * tile leave their entry untouched.  max_wg == 0 turns it off.  The
  * recording adds one barrier per workgroup. */
 MOE_API moe_status moe_profile_gemm_timeline(moe_ctx *ctx, uint64_t *gateup, uint64_t *down,

@@ -669,6 +669,7 @@ struct TilePos {
     int el;            // local expert, or -1 past the last tile
     int first, rows;   // its rows
     int n_sub, sub;    // its token tiles, and this one
+    int before;        // token tiles of the experts before it
     int ft;            // feature tile
 };
 
@@ -706,10 +707,10 @@ __device__ __forceinline__ TilePos find_tile(const GemmArgs& a, int block, int n
     t.first = __builtin_amdgcn_readlane(first, t.el);
     t.rows = __builtin_amdgcn_readlane(rows, t.el);
     t.n_sub = __builtin_amdgcn_readlane(n_sub, t.el);
-    const int before = __builtin_amdgcn_readlane(upto, t.el) - t.n_sub;
-    int in_left = at - before * n_left;
+    t.before = __builtin_amdgcn_readlane(upto, t.el) - t.n_sub;
+    int in_left = at - t.before * n_left;
     if (n_fg) {
-        const int in_e = pos - taken(before);
+        const int in_e = pos - taken(t.before);
         if (in_e < t.n_sub * n_fg) {
             t.sub = in_e % t.n_sub;
             t.ft = in_e / t.n_sub * kXcds + xcd;
@@ -717,7 +718,7 @@ __device__ __forceinline__ TilePos find_tile(const GemmArgs& a, int block, int n
         }
         // the left-over tiles as eight runs, the first for the XCD on which
         // the expert before it ended
-        const int q = (xcd + kXcds * n_left - before % kXcds * n_left) % kXcds;
+        const int q = (xcd + kXcds * n_left - t.before % kXcds * n_left) % kXcds;
         const int run = t.n_sub * n_left / kXcds, longer = t.n_sub * n_left % kXcds;
         in_left = q * run + min(q, longer) + in_e - t.n_sub * n_fg;
     }
@@ -734,7 +735,7 @@ __global__ __launch_bounds__(kThreads) void gemm_kernel(GemmArgs a)
     const int n_ftiles = M / BM;
     const TilePos tp = find_tile(a, blockIdx.x, n_ftiles, BN);
     if (tp.el < 0) return;
-    const int ft = tp.ft, tt = tp.sub, e = a.e_begin + tp.el;
+    const int ft = tp.ft, tt = tp.before + tp.sub, e = a.e_begin + tp.el;
     const int row_start = tp.first + tp.sub * BN, row_end = min(row_start + BN, tp.first + tp.rows);
     const bool stamp = a.stamps != nullptr && (int)blockIdx.x < a.max_stamps;
     uint64_t r0 = 0, c0 = 0;

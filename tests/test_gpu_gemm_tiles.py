@@ -97,3 +97,24 @@ def test_tiles_are_dealt_evenly_over_the_xcds(torch_mod, d, f, loads):
         per_xcd = np.bincount(np.nonzero(live)[0] % 8, minlength=8)
         assert per_xcd.max() - per_xcd.min() <= 1, per_xcd
     layer.close()
+
+
+def test_timeline_token_tiles_count_over_the_experts(torch_mod):
+    """The recorded token tile is its index among all local experts' tiles."""
+    torch = torch_mod
+    d, f, loads = 256, 128, (300, 0, 600, 5)
+    wl = mi.WORKLOADS["tiny"].with_(T=sum(loads), d=d, f=f, E=4, k=1, sigma_w=0.05)
+    layer = make_layer(wl)
+    load_workload_host(layer, wl)
+    x_t, _ = x_device(wl)
+    lg = np.zeros((wl.T, 4), np.float32)
+    lg[np.arange(wl.T), np.repeat(np.arange(4), loads)] = 4.0
+    buf = torch.zeros(64 * 8, dtype=torch.int64, device="cuda")
+    moe.moe_profile_gemm_timeline(layer.ctx, None, buf.data_ptr(), 64)
+    rt = layer.route(0, x_t, logits_in=torch.from_numpy(lg).cuda())
+    layer.forward(0, x_t, torch.empty((wl.T, d), dtype=torch.int16, device="cuda"), routing=rt)
+    torch.cuda.synchronize()
+    t = buf.cpu().numpy().view(np.uint64).reshape(64, 8)
+    got = sorted((int(v >> 16) & 0xFFFF, int(v >> 48), int(v >> 32) & 0xFFFF) for v in t[t[:, 1] > 0, 5])
+    assert got == [(0, 0, 256), (1, 0, 44), (2, 2, 256), (3, 2, 256), (4, 2, 88), (5, 3, 5)]
+    layer.close()
