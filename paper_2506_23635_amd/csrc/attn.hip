@@ -524,14 +524,13 @@ struct ScoreArgs {
 
 // The attention of up to 16 query rows per key/value head over at most 1024
 // positions (attn_short).  One workgroup of 4 waves per (key/value head g,
-// chunk c of 64 positions);
-// wave w owns positions 16 w .. 16 w + 15 of the chunk.  The query rows are
-// every (token t, query head j of g), r = t * group + jj, in batches of 16;
-// row r sees positions up to pos0 + t (causal).
+// chunk c of 64 positions); wave w owns positions 16 w .. 16 w + 15 of the
+// chunk.  The query rows are every (token t, query head j of g), r = t * group
+// + jj < 16; row r sees positions up to pos0 + t (causal).
 //
 // Scores on the matrix cores: v_mfma_f32_16x16x32_bf16 with the wave's 16
 // positions x 32 dims of K as the A operand (lane l: position l%16, dims
-// 8(l/16)..+7) and the batch's q rows as B, so lane l ends with the scores of
+// 8(l/16)..+7) and the q rows as B, so lane l ends with the scores of
 // query row l%16 at positions 16 w + 4(l/16) + i (i = 0..3).  The chunk's
 // maximum per row is the maximum of the four waves' (two butterfly steps in
 // the wave, then LDS), exp(s - max) goes to LDS and the chunk's sum adds the
@@ -578,100 +577,95 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a)
             p < last ? ld16(vbase + (int64_t)(p0 + p) * HD + k8 * 8) : zero;
     }
     const int dg = lane & 15, pq = lane >> 4;
-    for (int b0 = 0; b0 < R; b0 += 16) {
-        const int c_row = b0 + dg;                      // this lane's query row
-        const bool row_ok = c_row < R;
-        const int t_row = row_ok ? c_row / group : 0;
-        const int j_row = g * group + (row_ok ? c_row % group : 0);
-        const uint16_t* qrow = a.q + ((int64_t)t_row * a.H + j_row) * HD + pq * 8;
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    const bool row_ok = dg < R;                         // this lane's query row
+    const int t_row = row_ok ? dg / group : 0;
+    const int j_row = g * group + (row_ok ? dg % group : 0);
+    const uint16_t* qrow = a.q + ((int64_t)t_row * a.H + j_row) * HD + pq * 8;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const u32x4_t qb = row_ok ? ld16(qrow + ks * 32) : zero;
-            acc = moe::mfma16x16x32(kf[ks], qb, acc);
-        }
-        // scale, causal mask, the chunk's maximum per row
-        const int lim = a.pos0 + t_row;
-        float sv[4];
-        float m = -INFINITY;
+    for (int ks = 0; ks < KS; ++ks) {
+        const u32x4_t qb = row_ok ? ld16(qrow + ks * 32) : zero;
+        acc = moe::mfma16x16x32(kf[ks], qb, acc);
+    }
+    // scale, causal mask, the chunk's maximum per row
+    const int lim = a.pos0 + t_row;
+    float sv[4];
+    float m = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int pos = p0 + w * 16 + pq * 4 + i;
-            sv[i] = (row_ok && pos <= lim) ? acc[i] * a.scale : -INFINITY;
-            m = fmaxf(m, sv[i]);
-        }
-        m = fmaxf(m, __shfl_xor(m, 16, 64));
-        m = fmaxf(m, __shfl_xor(m, 32, 64));
-        if (lane < 16) mx[w][lane] = m;
-        __syncthreads();
-        m = fmaxf(fmaxf(mx[0][dg], mx[1][dg]), fmaxf(mx[2][dg], mx[3][dg]));
-        float l = 0.f;
+    for (int i = 0; i < 4; ++i) {
+        const int pos = p0 + w * 16 + pq * 4 + i;
+        sv[i] = (row_ok && pos <= lim) ? acc[i] * a.scale : -INFINITY;
+        m = fmaxf(m, sv[i]);
+    }
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if (lane < 16) mx[w][lane] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(mx[0][dg], mx[1][dg]), fmaxf(mx[2][dg], mx[3][dg]));
+    float l = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float p = sv[i] == -INFINITY ? 0.f : expf(sv[i] - m);
-            l += p;
-            ps[dg][w * 16 + pq * 4 + i] = p;
-        }
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
-        if (lane < 16) lx[w][lane] = l;
-        __syncthreads();
-        // row statistics of the chunk: wave 0, lanes of the first position group
-        if (w == 0 && pq == 0 && row_ok) {
-            float* out = a.part + (((int64_t)t_row * a.H + j_row) * a.n_chunks + c) * (HD + kPartPad);
-            out[HD] = m;
-            out[HD + 1] = ((lx[0][dg] + lx[1][dg]) + lx[2][dg]) + lx[3][dg];
-        }
-        // P v for this wave's quarter of the dims, 8 rows at a time
-        const int nb = min(16, R - b0);
-        for (int r0 = 0; r0 < nb; r0 += 8) {
-            float o[8][D];
+    for (int i = 0; i < 4; ++i) {
+        const float p = sv[i] == -INFINITY ? 0.f : expf(sv[i] - m);
+        l += p;
+        ps[dg][w * 16 + pq * 4 + i] = p;
+    }
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (lane < 16) lx[w][lane] = l;
+    __syncthreads();
+    // row statistics of the chunk: wave 0, lanes of the first position group
+    if (w == 0 && pq == 0 && row_ok) {
+        float* out = a.part + (((int64_t)t_row * a.H + j_row) * a.n_chunks + c) * (HD + kPartPad);
+        out[HD] = m;
+        out[HD + 1] = ((lx[0][dg] + lx[1][dg]) + lx[2][dg]) + lx[3][dg];
+    }
+    // P v for this wave's quarter of the dims, 8 rows at a time
+    for (int r0 = 0; r0 < R; r0 += 8) {
+        float o[8][D];
 #pragma unroll
-            for (int rr = 0; rr < 8; ++rr)
+        for (int rr = 0; rr < 8; ++rr)
 #pragma unroll
-                for (int e = 0; e < D; ++e) o[rr][e] = 0.f;
+            for (int e = 0; e < D; ++e) o[rr][e] = 0.f;
 #pragma unroll 4
-            for (int k = 0; k < kPos / 4; ++k) {
-                const int p = 4 * k + pq;
-                const uint16_t* vr = &vs[p * VROW + w * DQ + dg * D];
-                float vv[D];
-                if constexpr (D == 2) {
-                    const uint32_t w2 = *reinterpret_cast<const uint32_t*>(vr);
-                    vv[0] = __uint_as_float(w2 << 16);
-                    vv[1] = __uint_as_float(w2 & 0xFFFF0000u);
-                } else {
-                    vv[0] = __uint_as_float((uint32_t)vr[0] << 16);
-                }
-#pragma unroll
-                for (int rr = 0; rr < 8; ++rr) {
-                    const float pw = ps[r0 + rr][p];
-#pragma unroll
-                    for (int e = 0; e < D; ++e) o[rr][e] = fmaf(pw, vv[e], o[rr][e]);
-                }
+        for (int k = 0; k < kPos / 4; ++k) {
+            const int p = 4 * k + pq;
+            const uint16_t* vr = &vs[p * VROW + w * DQ + dg * D];
+            float vv[D];
+            if constexpr (D == 2) {
+                const uint32_t w2 = *reinterpret_cast<const uint32_t*>(vr);
+                vv[0] = __uint_as_float(w2 << 16);
+                vv[1] = __uint_as_float(w2 & 0xFFFF0000u);
+            } else {
+                vv[0] = __uint_as_float((uint32_t)vr[0] << 16);
             }
 #pragma unroll
-            for (int rr = 0; rr < 8; ++rr)
+            for (int rr = 0; rr < 8; ++rr) {
+                const float pw = ps[r0 + rr][p];
 #pragma unroll
-                for (int e = 0; e < D; ++e) {
-                    float v = o[rr][e];
-                    v += __shfl_xor(v, 16, 64);
-                    v += __shfl_xor(v, 32, 64);
-                    o[rr][e] = v;
-                }
-            if (pq == 0) {
+                for (int e = 0; e < D; ++e) o[rr][e] = fmaf(pw, vv[e], o[rr][e]);
+            }
+        }
 #pragma unroll
-                for (int rr = 0; rr < 8; ++rr) {
-                    const int r = b0 + r0 + rr;
-                    if (r < R) {
-                        const int t = r / group, j = g * group + r % group;
-                        float* out = a.part + (((int64_t)t * a.H + j) * a.n_chunks + c) * (HD + kPartPad);
+        for (int rr = 0; rr < 8; ++rr)
 #pragma unroll
-                        for (int e = 0; e < D; ++e) out[w * DQ + dg * D + e] = o[rr][e];
-                    }
+            for (int e = 0; e < D; ++e) {
+                float v = o[rr][e];
+                v += __shfl_xor(v, 16, 64);
+                v += __shfl_xor(v, 32, 64);
+                o[rr][e] = v;
+            }
+        if (pq == 0) {
+#pragma unroll
+            for (int rr = 0; rr < 8; ++rr) {
+                const int r = r0 + rr;
+                if (r < R) {
+                    const int t = r / group, j = g * group + r % group;
+                    float* out = a.part + (((int64_t)t * a.H + j) * a.n_chunks + c) * (HD + kPartPad);
+#pragma unroll
+                    for (int e = 0; e < D; ++e) out[w * DQ + dg * D + e] = o[rr][e];
                 }
             }
         }
-        __syncthreads();
     }
 }
 
