@@ -8,6 +8,7 @@ flash_kernel in blocks of 64 (up to 64 rows) or 128 rows and steps of 64
 positions, in one or several ranges."""
 import pytest
 
+import paper_2506_23635_amd as moe
 from test_gpu_attn import TINY, Case, check_block, torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -58,5 +59,51 @@ def test_projection_tile_pairs(torch_mod, d, H, G, hd, T, pos0):  # noqa: F811
         kc, vc = case.cache()
         check_block(case, x, pos0, y, case.layer.intermediates(T), kc, vc)
         assert (case.forward(x, pos0) == y).all()
+    finally:
+        case.close()
+
+
+# several ranges of several steps: at most 1024 workgroups and 128 ranges, so
+# these positions leave every range three steps or more, and unevenly many
+@pytest.mark.parametrize("H,G,hd,T,pos0", [
+    (8, 1, 128, 8, 25000),     # 64 rows: two position groups; at most 128 ranges of 391 steps
+    (8, 1, 128, 16, 25000),    # 128 rows: one
+    (32, 16, 64, 16, 12500),   # 32 rows; at most 64 ranges of 196 steps
+    (96, 16, 64, 16, 12500),   # 96 rows
+])
+def test_ranges_of_several_steps(torch_mod, H, G, hd, T, pos0):  # noqa: F811
+    wl = TINY.with_(d=256, n_heads=H, n_kv=G, hd=hd, T=T, pos0=pos0, max_seq=pos0 + T + 7)
+    case = Case(torch_mod, wl, max_tokens=16)
+    try:
+        x = wl.x()
+        moe.attn_profile_enable(case.layer.ctx, 16)
+        y = case.forward(x, pos0)
+        launches = {k: n for k, (_, n) in moe.attn_profile_read(case.layer.ctx)[0].items()}
+        assert launches["combine"] == 1            # several ranges, merged
+        moe.attn_profile_enable(case.layer.ctx, 0)
+        kc, vc = case.cache()
+        check_block(case, x, pos0, y, case.layer.intermediates(T), kc, vc)
+        assert (case.forward(x, pos0) == y).all()
+    finally:
+        case.close()
+
+
+# the prefill projections on 256 x 256 tiles (from 129 tiles on: 32 feature
+# tiles, five token tiles) with a partial last token tile: of one 32-row block,
+# of up to 128 rows, and of more
+@pytest.mark.parametrize("T", [1044, 1124, 1244])
+@pytest.mark.parametrize("d,H,G", [(256, 64, 32), (8192, 4, 4)])   # q|k|v; output
+def test_projection_tile_tails(torch_mod, d, H, G, T):  # noqa: F811
+    wl = TINY.with_(d=d, n_heads=H, n_kv=G, hd=64, T=T, pos0=3, max_seq=T + 8)
+    case = Case(torch_mod, wl, max_tokens=T)
+    try:
+        x = wl.x()
+        moe.attn_profile_enable(case.layer.ctx, 16)
+        y = case.forward(x, 3)
+        launches = {k: n for k, (_, n) in moe.attn_profile_read(case.layer.ctx)[0].items()}
+        assert launches["rope" if d == 256 else "residual"] == 0   # the end is the projection's own
+        moe.attn_profile_enable(case.layer.ctx, 0)
+        kc, vc = case.cache()
+        check_block(case, x, 3, y, case.layer.intermediates(T), kc, vc)
     finally:
         case.close()
