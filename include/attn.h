@@ -47,7 +47,7 @@ typedef struct attn_ctx attn_ctx;
  *   max_seq    : cache positions per layer (>= 1).
  *   max_tokens : largest T of a call, 1 .. 32768.  Up to 16 tokens a call
  *                takes the decode path (weight-streaming GEMVs, attention
- *                over position chunks); above, the prefill path (matrix-core
+ *                over position chunks or ranges); above, the prefill path (matrix-core
  *                GEMMs for the projections, causal attention on the matrix
  *                cores), which needs (n_heads + 2 n_kv_heads) head_dim to be
  *                a multiple of 256 when max_tokens > 16.
@@ -127,13 +127,13 @@ MOE_API moe_status attn_intermediates(const attn_ctx *ctx, const uint16_t **h, c
  * kinds of attn_kernel_kind. */
 typedef enum {
     ATTN_K_NORM = 0,       /* layer norm */
-    ATTN_K_QKV = 1,        /* fused projection (+ rotary + cache append in decode) */
-    ATTN_K_SCORE = 2,      /* attention (over position chunks in decode, causal in prefill) */
-    ATTN_K_COMBINE = 3,    /* merge of the chunks (decode) */
-    ATTN_K_OUT = 4,        /* output projection (+ residual in decode) */
+    ATTN_K_QKV = 1,        /* fused projection (+ rotary + cache append, unless split) */
+    ATTN_K_SCORE = 2,      /* causal attention (over position chunks or ranges) */
+    ATTN_K_COMBINE = 3,    /* merge of the chunks or ranges (not with one range) */
+    ATTN_K_OUT = 4,        /* output projection (+ residual, unless split) */
     ATTN_K_PACK = 5,       /* weight repacking */
-    ATTN_K_ROPE = 6,       /* rotary + cache append (prefill) */
-    ATTN_K_RESIDUAL = 7,   /* y = bf16(x + o) (prefill) */
+    ATTN_K_ROPE = 6,       /* rotary + cache append (prefill, split projection) */
+    ATTN_K_RESIDUAL = 7,   /* y = bf16(x + o) (prefill, split projection) */
     ATTN_K_POST_NORM = 8,  /* z = norm(y) (attn_forward_norm) */
     ATTN_K_COUNT = 9
 } attn_kernel_kind;

@@ -244,12 +244,13 @@ MOE_API moe_status moe_forward_residual(moe_ctx *ctx, int32_t layer, const uint1
  * (alignment padding) are never written.  Fills min(n, MOE_WS_COUNT)
  * entries and returns MOE_WS_COUNT, or 0 if cfg is invalid. */
 typedef enum {
-    MOE_WS_ROUTE_PARTIALS = 0, /* fp64 partial logits of the small-T router */
+    MOE_WS_ROUTE_PARTIALS = 0, /* fp64 partial logits of the small-T router (unused at d <= 512) */
     MOE_WS_LOGITS, MOE_WS_TOPK_IDX, MOE_WS_TOPK_W, MOE_WS_COUNTS, MOE_WS_OFFSETS,
     MOE_WS_PAIR_ROW, MOE_WS_ROW_TOKEN,
     MOE_WS_ACTIVE,             /* int32 [1 + E]: #active local experts, their ids */
-    MOE_WS_TILES,              /* int32 [max_tiles][2]: GEMM token tiles */
-    MOE_WS_N_TILES,            /* int32 [1] */
+    MOE_WS_TILES,              /* int32 [max_tiles][2]: token tiles of 256 rows (expert, first row);
+                                  for inspection, no kernel reads them */
+    MOE_WS_N_TILES,            /* int32 [1], likewise */
     MOE_WS_H,                  /* bf16 [rows_max, f] */
     MOE_WS_O,                  /* fp32 [rows_max, d] */
     MOE_WS_COUNT

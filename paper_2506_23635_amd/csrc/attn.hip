@@ -1116,8 +1116,9 @@ __global__ __launch_bounds__(256, 2) void flash_kernel(FlashArgs a)
         }
         return;
     }
-    // few tokens divide, as merge_kernel does, so that a token's bits do not
-    // depend on whether the positions come in one range or several
+    // few tokens divide, as merge_kernel does.  (The bits still depend on the
+    // number of ranges: each takes its own maximum, and their sums are added
+    // in range order.)
     const float inv = 1.0f / l;
     auto norm = [&](float v) { return kTerms == 3 ? v / l : v * inv; };
     uint16_t* dst = a.out + ((int64_t)t * a.H + j) * HD + 4 * h;
@@ -1362,10 +1363,11 @@ int attn_part_max(int T, int H, int G, int max_seq)
 // A workgroup costs its steps and about two more; 512 run at a time, in
 // rounds that are cut short as far as the row blocks differ in length; the
 // partial sums are written and read at about 5 TB/s.  Measured (DBRX block,
-// whole call, one range -> the chosen count): 16 tokens after 16000 positions
-// 219 -> 88 us (64 ranges; 32: 89, 128: 103), 64 after 8000 426 -> 123 (32;
-// 16: 134, 64: 141), 300 after 1000 189 -> 161 (4; 2: 168, 8: 169), 512 after
-// 8000 528 -> 367 (5; 2: 385); 1024 from empty 306 (1; 2: 339).
+// whole call, by the number of ranges): 16 tokens after 16000 positions 219 us
+// (1), 89 (32), 88 (64), 103 (128), it takes 63; 64 after 8000 426 (1), 134
+// (16), 123 (32), 141 (64), it takes 18, which is too few; 300 after 1000 189
+// (1), 168 (2), 161 (4), 169 (8), it takes 3; 512 after 8000 528 (1), 385 (2),
+// 367 (5), it takes 5; 1024 from empty 306 (1), 339 (2), it takes 1.
 int attn_split(int T, int H, int G, int pos0, int max_seq)
 {
     const int pg = flash_pg(T, H, G), rows = attn::flash_rows(pg), step = attn::kFlashP;

@@ -3,10 +3,11 @@
 // weight repack (the query and key heads of Wqkv with their rotation pairs
 // in one tile), and the launch sequences of the block: up to 16 tokens
 // (decode) norm, inside the projection up to 4 tokens -> fused projection +
-// rotary + cache append -> attention over position chunks -> merge ->
-// output projection + residual; above 16 (prefill) norm -> projection GEMM
-// -> rotary + cache append -> causal attention -> output GEMM -> residual.
-// Nothing here allocates device memory.
+// rotary + cache append -> attention over position chunks or ranges -> merge
+// -> output projection + residual; above 16 (prefill) norm -> projection GEMM
+// + rotary + cache append -> causal attention, merged where it is in ranges ->
+// output GEMM + residual, the ends of the two GEMMs in kernels of their own
+// where their reductions are split.  Nothing here allocates device memory.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -16,8 +16,10 @@
 //   route_partials_kernel + route_finish_kernel (T <= 16, E <= 16,
 //       T*k <= 64): partial logits over a few workgroups, then one workgroup
 //       sums them in fixed order, selects and permutes.
+//   route_one_kernel: both in one launch where one workgroup forms the logits
+//       anyway (d <= 512).
 //   select_kernel: selection and weights from caller-supplied fp32 logits.
-//   permute_kernel: the permutation and the GEMM tile list (one workgroup).
+//   permute_kernel: the permutation and the list of token tiles (one workgroup).
 //
 // Selection: the k largest logits, ties to the lower expert id, slots ordered
 // by (logit desc, id asc); weights = softmax over the selected logits (fp32).
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ l
 // Expert-grouped permutation of the T*k pairs (one 1024-thread workgroup),
 // rows grouped by local expert, then by pair (token, slot) order.
 //  1. counts: LDS histogram of the local pairs (order-free); thread 0 then
-//     writes counts, offsets, the active-expert list and the GEMM tile list.
+//     writes counts, offsets, the active-expert list and the token tiles.
 //  2. rows: pairs in rounds of 1024 x 8; each thread holds 8 consecutive
 //     pairs; per group of 16 experts, one wave scan of packed per-thread
 //     counts plus a scan of the wave totals give each pair its row after the
