@@ -14,8 +14,10 @@ arithmetic:
   y    = bf16(fp32(x + o_gpu)) exactly (the kernel's residual rounding);
 and end to end: o and y against the oracle block (relative L2 <= 2e-3,
 max-abs <= 1e-2 max(1, max|ref|)).  T tokens at once equal T single-token
-steps bit for bit, the cache changes only at the new positions, and repeated
-calls give the same bits."""
+steps bit for bit where both take the attention over chunks (up to 16 rows
+per key/value head and 1024 positions; beyond, the number of position ranges
+depends on T), the cache changes only at the new positions, and repeated calls
+give the same bits."""
 import numpy as np
 import pytest
 

@@ -68,8 +68,8 @@ def test_projection_tile_pairs(torch_mod, d, H, G, hd, T, pos0):  # noqa: F811
 @pytest.mark.parametrize("H,G,hd,T,pos0", [
     (8, 1, 128, 8, 25000),     # 64 rows: two position groups; at most 128 ranges of 391 steps
     (8, 1, 128, 16, 25000),    # 128 rows: one
-    (32, 16, 64, 16, 12500),   # 32 rows; at most 64 ranges of 196 steps
-    (96, 16, 64, 16, 12500),   # 96 rows
+    (32, 16, 64, 16, 12600),   # 32 rows; at most 64 ranges of 198 steps
+    (96, 16, 64, 16, 12600),   # 96 rows
 ])
 def test_ranges_of_several_steps(torch_mod, H, G, hd, T, pos0):  # noqa: F811
     wl = TINY.with_(d=256, n_heads=H, n_kv=G, hd=hd, T=T, pos0=pos0, max_seq=pos0 + T + 7)
