@@ -61,9 +61,9 @@ __device__ inline u32x4_t ld16_nt(const void* p)
 
 __device__ inline u32x4_t ld16(const void* p) { return *reinterpret_cast<const u32x4_t*>(p); }
 
-// The full batches of a projection's reduction with the tokens in memory:
-// kUnrollX K tiles per wave and batch, weights and token fragments in two
-// buffers in turn, the next batch's loads issued before this batch's MFMAs,
+// A projection's reduction with the tokens in memory: kUnrollX K tiles per
+// wave and batch, weights and token fragments in two buffers in turn, the next
+// batch's loads issued before this batch's MFMAs,
 // so that both stay in flight while it is multiplied.  (With the token
 // fragments loaded in their own batch every batch waited one cache latency
 // for them: with this and the epilogues' loads and rotations ahead of the
@@ -71,13 +71,18 @@ __device__ inline u32x4_t ld16(const void* p) { return *reinterpret_cast<const u
 // 16 tokens after 100 66.8 -> 64.8; three tiles per batch 41.9 and 64.0, but
 // 24.6 against 23.8 at d 2048; six 42.3 and 66.8.)  The loads have no branches (an unused column reads token
 // 0's row and feeds zeros), so a wait for them is not a wait for everything.
+// The remainder is a shorter batch (tile after tile, every one waited for its
+// loads, and a reduction shorter than a batch formed its rotations before any
+// load: 32 heads of 128 without groups, 5 tokens, d 768 26.8 -> 25.2 us, d 1536
+// 28.7 -> 26.4).
 // kS row tiles, `slab` bytes apart, share each token fragment.
-// kt: K tiles done; `meanwhile` runs once while the first loads are in flight.
+// `meanwhile` runs once while the first loads are in flight.
 template <int kS, class F>
-__device__ __forceinline__ void stream_batches(const uint8_t* pw, int64_t slab, const uint16_t* px, int nb,
-                                               int w, bool has_tok, f32x4_t (&acc)[kS], int& kt, F&& meanwhile)
+__device__ __forceinline__ void stream_batches(const uint8_t* pw, int64_t slab, const uint16_t* px, int KT,
+                                               int w, bool has_tok, f32x4_t (&acc)[kS], F&& meanwhile)
 {
     constexpr int kStep = kSplit * kUnrollX;
+    const int nb = KT / kStep;
     const u32x4_t zero = {0u, 0u, 0u, 0u};
     auto load = [&](int b, u32x4_t* wt, u32x4_t* xv) {
 #pragma unroll
@@ -95,11 +100,35 @@ __device__ __forceinline__ void stream_batches(const uint8_t* pw, int64_t slab, 
             for (int c = 0; c < kS; ++c)
                 acc[c] = moe::mfma16x16x32(wt[u * kS + c], has_tok ? xv[u] : zero, acc[c]);
     };
+    // the K tiles past the last full batch (K is a multiple of 256, so every
+    // wave has as many)
+    const int n_rest = (KT - nb * kStep) / kSplit;
+    auto rest = [&](u32x4_t* wt, u32x4_t* xv) {
+#pragma unroll
+        for (int u = 0; u + 1 < kUnrollX; ++u)
+            if (u < n_rest) {
+                xv[u] = ld16(px + (nb * kStep + w + kSplit * u) * kTileK);
+#pragma unroll
+                for (int c = 0; c < kS; ++c)
+                    wt[u * kS + c] = ld16_nt(pw + c * slab + (int64_t)(nb * kStep + w + kSplit * u) * kTileBytes);
+            }
+    };
+    auto rest_mfmas = [&](const u32x4_t* wt, const u32x4_t* xv) {
+#pragma unroll
+        for (int u = 0; u + 1 < kUnrollX; ++u)
+            if (u < n_rest) {
+#pragma unroll
+                for (int c = 0; c < kS; ++c)
+                    acc[c] = moe::mfma16x16x32(wt[u * kS + c], has_tok ? xv[u] : zero, acc[c]);
+            }
+    };
+    u32x4_t wa[kUnrollX * kS], wb[kUnrollX * kS], xa[kUnrollX], xb[kUnrollX];
     if (nb == 0) {
+        rest(wa, xa);
         meanwhile();
+        rest_mfmas(wa, xa);
         return;
     }
-    u32x4_t wa[kUnrollX * kS], wb[kUnrollX * kS], xa[kUnrollX], xb[kUnrollX];
     load(0, wa, xa);
     meanwhile();
     int b = 0;
@@ -112,11 +141,14 @@ __device__ __forceinline__ void stream_batches(const uint8_t* pw, int64_t slab, 
     if (b + 1 < nb) {
         load(b + 1, wb, xb);
         mfmas(wa, xa);
+        rest(wa, xa);
         mfmas(wb, xb);
+        rest_mfmas(wa, xa);
     } else {
+        rest(wb, xb);
         mfmas(wa, xa);
+        rest_mfmas(wb, xb);
     }
-    kt = nb * kStep;
 }
 
 // The output projection, o = a Wo (fp32) and y = bf16(x + o), one
@@ -143,21 +175,13 @@ __global__ __launch_bounds__(64 * kSplit) void gemv_kernel(GemvArgs a)
     const bool has_tok = j < a.T;
     const uint16_t* px = a.x + (has_tok ? (int64_t)j * a.K : 0) + g * 8;
     f32x4_t acc[kS] = {};
-    const u32x4_t zero = {0u, 0u, 0u, 0u};
     // wave c < kS ends row tile q + c.  The residual of its lanes' outputs,
     // loaded ahead of the weights (output features 16 (q + c) + 4g .. +3 of
     // token j; other lanes read token 0's)
     const int c = min(w, kS - 1);
     const int64_t o = (int64_t)(has_tok ? j : 0) * a.N + (q + c) * kTileRows + g * 4;
     const uint2 r = *reinterpret_cast<const uint2*>(a.res + o);
-    int kt = 0;
-    stream_batches<kS>(pw, slab, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, [] {});
-    for (kt += w; kt < KT; kt += kSplit) {
-        const u32x4_t xt = has_tok ? ld16(px + kt * kTileK) : zero;
-#pragma unroll
-        for (int i = 0; i < kS; ++i)
-            acc[i] = moe::mfma16x16x32(ld16_nt(pw + i * slab + (int64_t)kt * kTileBytes), xt, acc[i]);
-    }
+    stream_batches<kS>(pw, slab, px, KT, w, has_tok, acc, [] {});
 #pragma unroll
     for (int i = 0; i < kS; ++i) s_red[i][w * 64 + lane] = acc[i];
     __syncthreads();
@@ -416,9 +440,8 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
         }
         lds_barrier();
     }
-    int kt = 0;
     if constexpr (!kNorm) {
-        stream_batches<kS>(pw, slab, px, KT / (kSplit * kUnrollX), w, has_tok, acc, kt, rotations);
+        stream_batches<kS>(pw, slab, px, KT, w, has_tok, acc, rotations);
     } else {
         // two weight buffers in turn (the first batch was issued above, into
         // wv), tokens from LDS
@@ -460,18 +483,11 @@ __global__ __launch_bounds__(64 * kSplit) void qkv_kernel(QkvArgs a)
             } else {
                 mfmas(wv, xb);
             }
-            kt = nb * kStep;
         }
-    }
-    for (kt += w; kt < KT; kt += kSplit) {
-        u32x4_t xt;
-        if constexpr (kNorm)
-            xt = has_tok ? *reinterpret_cast<const u32x4_t*>(hx + kt * kTileK) : zero;
-        else
-            xt = has_tok ? ld16(px + kt * kTileK) : zero;
-#pragma unroll
-        for (int i = 0; i < kS; ++i)
-            acc[i] = moe::mfma16x16x32(ld16_nt(pw + i * slab + (int64_t)kt * kTileBytes), xt, acc[i]);
+        for (int kt = nb * kStep + w; kt < KT; kt += kSplit) {
+            const u32x4_t xt = has_tok ? *reinterpret_cast<const u32x4_t*>(hx + kt * kTileK) : zero;
+            acc[0] = moe::mfma16x16x32(ld16_nt(pw + (int64_t)kt * kTileBytes), xt, acc[0]);
+        }
     }
 #pragma unroll
     for (int i = 0; i < kS; ++i) s_red[i][w * 64 + lane] = acc[i];
