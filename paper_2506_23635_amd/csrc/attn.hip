@@ -1283,12 +1283,29 @@ int attn_norm_in_projection(int T) { return T <= attn::kLnMaxT; }
 
 // Two row tiles per workgroup in the decode projections: each token fragment,
 // as many bytes as a weight tile's and read by every workgroup, then serves
-// two tiles.  It pays where the halved grid still covers three quarters of the
-// CUs (16 tokens: 512 + 384 tiles 63.9 -> 55.3 us for the block, 384 of q|k|v
-// alone 39.1 -> 38.1; 256 of the output alone 39.1 -> 41.7, 192 of q|k|v 23.8
-// -> 25.0, 128 of the output 23.8 -> 25.4).  One token, whose q|k|v reads its
-// fragments from LDS: the output projection alone 41.3 -> 40.5.
-static bool two_tiles(int tiles) { return tiles >= 384 && tiles % 2 == 0; }
+// two tiles.  It pays
+//  - where the halved grid covers three quarters of the CUs once, or all at
+//    least twice (16 tokens of the DBRX block: 512 + 384 tiles 63.9 -> 55.3 us;
+//    q|k|v of 1024 tiles at d 3072 54.2 -> 50.4; 256 of the output 39.1 -> 41.7,
+//    192 of q|k|v 23.8 -> 25.0; in between, eight tokens, 640 tiles at d 3072
+//    41.1 -> 43.0, 768 33.9 -> 35.4);
+//  - from two batches of K on, or one where more than 8 tokens' fragments count
+//    for more: shorter, it only takes loads out of flight (8 tokens, 512 tiles,
+//    d 768 27.2 -> 28.6; d 1024, 1024 tiles, 8 tokens 32.9 -> 32.4, 16 tokens
+//    37.7 -> 35.8);
+//  - not at K 4096, where the row tiles lie 128 KiB apart (their loads seem to
+//    meet in the same memory channels; 8 tokens, 512 tiles at d 4096 37.8 ->
+//    40.0, 1024 53.1 -> 58.2), but with few tiles and more than 8 tokens' fragments
+//    (384 tiles, 5 tokens 25.7 -> 26.7, 16 tokens 33.5 -> 31.4; 512 of
+//    q|k|v, 12 tokens 41.9 -> 43.2; 512 of the output at d 8192, 9 tokens 68.5 -> 71.2).
+// One token, whose q|k|v reads its fragments from LDS: the output projection
+// alone 41.3 -> 40.5.
+static bool two_tiles(int tiles, int K, int T)
+{
+    if (K < (T > 8 ? 1024 : 2048) || tiles < 384 || tiles % 2 != 0) return false;
+    if (K == 4096) return tiles < 512 && T > 8;
+    return tiles <= 512 || tiles >= 1024;
+}
 
 hipError_t attn_launch_qkv(const void* w, uint16_t* h, const uint16_t* x, const float* gamma,
                            float eps, const double* inv_freq, float* qkv, uint16_t* q,
@@ -1304,7 +1321,7 @@ hipError_t attn_launch_qkv(const void* w, uint16_t* h, const uint16_t* x, const 
         hipLaunchKernelGGL((attn::qkv_kernel<true, 1>), grid, block, lds, s, a);
     } else {
         // (H + 2 G) hd is a multiple of 64: the row tiles are even in number
-        if (two_tiles(grid.x)) hipLaunchKernelGGL((attn::qkv_kernel<false, 2>), dim3(grid.x / 2), block, 0, s, a);
+        if (two_tiles(grid.x, d, T)) hipLaunchKernelGGL((attn::qkv_kernel<false, 2>), dim3(grid.x / 2), block, 0, s, a);
         else hipLaunchKernelGGL((attn::qkv_kernel<false, 1>), grid, block, 0, s, a);
     }
     return hipGetLastError();
@@ -1316,7 +1333,7 @@ hipError_t attn_launch_out(const void* w, const uint16_t* x, int T, int K, int N
     attn::GemvArgs a{static_cast<const uint8_t*>(w), x, y32, res, y16, K, N, T};
     const int tiles = N / moe::kTileRows;
     const dim3 block(64 * attn::kSplit);
-    if (two_tiles(tiles)) hipLaunchKernelGGL(attn::gemv_kernel<2>, dim3(tiles / 2), block, 0, s, a);
+    if (two_tiles(tiles, K, T)) hipLaunchKernelGGL(attn::gemv_kernel<2>, dim3(tiles / 2), block, 0, s, a);
     else hipLaunchKernelGGL(attn::gemv_kernel<1>, dim3(tiles), block, 0, s, a);
     return hipGetLastError();
 }

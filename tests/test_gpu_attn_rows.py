@@ -40,15 +40,25 @@ def test_row_and_range_edges(torch_mod, H, G, hd, T, pos0):  # noqa: F811
         case.close()
 
 
-# the decode projections take two row tiles per workgroup from 384 tiles on
-# (q|k|v: (H + 2G) hd / 16 tiles over d; output: d / 16 tiles over H hd), in
-# batches of 32 K tiles of 32
+# the decode projections take one or two row tiles per workgroup (q|k|v: (H +
+# 2G) hd / 16 tiles over d; output: d / 16 tiles over H hd), in batches of 32 K
+# tiles of 32 and a shorter one: two from K 2048 (more than 8 tokens: 1024) and
+# 384 tiles on, but not between 512 and 1024 tiles, and at K 4096 only below 512
+# tiles and for more than 8 tokens
 @pytest.mark.parametrize("d,H,G,hd,T,pos0", [
     (512, 60, 15, 64, 16, 0),      # q|k|v 360 tiles: one per workgroup
-    (512, 32, 8, 128, 16, 70),     # 384 tiles: two, heads of both halves; half a batch of K
-    (1280, 32, 8, 128, 5, 1500),   # one batch and a remainder
-    (6144, 36, 6, 64, 9, 30),      # output 384 tiles, two batches and a remainder
-    (6144, 4, 4, 64, 1, 3),        # one token: output in pairs, less than a batch
+    (512, 32, 8, 128, 16, 70),     # 384 tiles, half a batch of K: one
+    (1280, 32, 8, 128, 5, 1500),   # one batch and a remainder: one; output K 4096
+    (6144, 36, 6, 64, 9, 30),      # output 384 tiles, two batches and a remainder: two
+    (6144, 4, 4, 64, 1, 3),        # one token: output 384 tiles, less than a batch: one
+    (256, 32, 8, 128, 5, 5),       # a remainder of one K tile per wave only
+    (1024, 32, 8, 128, 9, 7),      # one batch, nine tokens: two
+    (1280, 32, 8, 128, 16, 20),    # ... and a remainder, heads of both halves
+    (2304, 48, 8, 128, 5, 30),     # 512 tiles, two batches and a remainder: two
+    (2816, 64, 8, 128, 16, 4),     # 640 tiles, a remainder of three: one
+    (2048, 64, 32, 128, 7, 9),     # 1024 tiles: two
+    (4096, 32, 8, 128, 8, 40),     # K 4096: one
+    (4096, 32, 8, 128, 9, 40),     # ... and two
 ])
 def test_projection_tile_pairs(torch_mod, d, H, G, hd, T, pos0):  # noqa: F811
     wl = TINY.with_(d=d, n_heads=H, n_kv=G, hd=hd, T=T, pos0=pos0, max_seq=2048)
